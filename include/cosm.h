@@ -377,7 +377,10 @@ typedef struct {
                               largest sum of |J| and |h| at a vertex < 1/2 turn): FP32 in
                               the streamed LDS forms on the grid schedule (the result is
                               the same bit for bit), FP16 / BF16 / FP16_PK in every form (the
-                              centred value y then lies in (-1, 1) between twists) */
+                              centred value y then lies in (-1, 1) between twists).
+                              FP32 in the LDS forms on the grid schedule leaves the wrap to
+                              the twists up to a bound of one turn, with the same result;
+                              this field keeps to the 1/2-turn bound */
 } cosm_info;
 int cosm_get_info(const cosm_state *s, cosm_info *out);
 

@@ -619,6 +619,7 @@ int cosm_reset(cosm_state *s, uint64_t seed, int64_t replica_offset) {
   s->seed = seed;
   s->rid0 = replica_offset;
   s->t = 0;
+  s->on_grid = true;
   return launch_init(s);
 }
 
@@ -755,6 +756,7 @@ int cosm_set_phases(cosm_state *s, int32_t unit, const double *in, int64_t t) {
   const size_t nr = (size_t)s->n * s->R;
   const double scale = unit == COSM_UNIT_TURNS ? 1.0 : unit == COSM_UNIT_DEGREES ? 360.0 : 2.0 * M_PI;
   std::vector<float> host(nr);
+  bool on_grid = true;
   for (int32_t r = 0; r < s->R; r++)
     for (int32_t i = 0; i < s->n; i++) {
       double x = in[(size_t)r * s->n + i] / scale;
@@ -763,6 +765,8 @@ int cosm_set_phases(cosm_state *s, int32_t unit, const double *in, int64_t t) {
       float f = (float)x;
       if (f >= 1.0f) f = 0.0f;
       host[(size_t)i * s->R + r] = f;
+      const float q = f * 8388608.0f;  // exact: a scaling by 2^23
+      on_grid = on_grid && q == std::floor(q);
     }
   float *tmp = nullptr;
   COSM_HIP_CHECK(hipMalloc(&tmp, nr * 4));
@@ -772,7 +776,10 @@ int cosm_set_phases(cosm_state *s, int32_t unit, const double *in, int64_t t) {
   if (!rc) rc = launch_from_turns(s, tmp);
   if (!rc) rc = sync(s);
   (void)hipFree(tmp);
-  if (!rc) s->t = t;
+  if (!rc) {
+    s->t = t;
+    s->on_grid = on_grid;
+  }
   return rc;
 }
 

@@ -50,7 +50,8 @@ Key make_key(const cosm_state &s) {
     mix((uint32_t)s.h_colour[(size_t)k]);
   }
   const int32_t variant = (s.sched.grid ? 1 : 0) |
-                          (s.sched.dwt_period > 0 && wrap_drift_turns(s) < 0.5 ? 2 : 0);
+                          (s.sched.dwt_period > 0 && wrap_drift_turns(s) < 0.5 ? 2 : 0) |
+                          (wrap_at_twists(s) ? 4 : 0);
   return Key{s.n, s.m, s.C, s.R, s.p.storage, s.p.lds_form, s.has_h ? 1 : 0, variant, h};
 }
 

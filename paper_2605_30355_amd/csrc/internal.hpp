@@ -231,6 +231,9 @@ struct cosm_state {
   uint64_t seed = 0;
   int64_t rid0 = 0;   // global index of replica 0
   int64_t t = 0;      // sweeps done
+  // every phase a multiple of 2^-23 turn: true after a draw under the grid
+  // schedule (the sweeps keep it so), checked when phases are set from outside
+  bool on_grid = true;
   hipStream_t stream = nullptr;
   bool own_memory = false;
   void *base = nullptr;
@@ -297,6 +300,11 @@ bool grid_parity_step(const cosm_state &s);
 // That drift bound in turns: the largest twist plus period x the largest step
 // x the largest sum of |J| and |h| at one vertex.
 double wrap_drift_turns(const cosm_state &s);
+// Whether the FP32 LDS sweeps under the parity step may leave the wrap of every
+// update to the twists: drift below one whole turn and phases on the grid
+// (kernels.hip).  Wider than lds_lazy_wrap's half turn, which also bounds the
+// forms without the parity step and is what cosm_info.lazy_wrap reports.
+bool wrap_at_twists(const cosm_state &s);
 int launch_readout(cosm_state *s);
 // Optimal-bisector readout (readout_opt.hip); h must be absent.
 int launch_readout_optimal(cosm_state *s);

@@ -373,7 +373,8 @@ int launch_sweeps_rstream(cosm_state *s, int64_t n_sweeps) {
   a.k1 = (uint32_t)(s->seed >> 32);
   a.rid0 = (uint32_t)s->rid0;
   const int W = s->shape.rw;  // FP32: one word per replica
-  if (lds_lazy_wrap(*s)) return launch_rstream_l<COSM_STORE_FP32, true>(s, a, W, L.reg_k);
+  if (lds_lazy_wrap(*s) || wrap_at_twists(*s))
+    return launch_rstream_l<COSM_STORE_FP32, true>(s, a, W, L.reg_k);
   return launch_rstream_l<COSM_STORE_FP32, false>(s, a, W, L.reg_k);
 }
 

@@ -359,7 +359,7 @@ template <int ST, int W>
 int launch_stream_w(cosm_state *s, const StreamArgs &a) {
   if constexpr (parity_storage(ST)) {
     if (grid_parity_step(*s)) {
-      if (lds_lazy_wrap(*s)) return launch_stream_l<ST, W, true, true>(s, a);
+      if (lds_lazy_wrap(*s) || wrap_at_twists(*s)) return launch_stream_l<ST, W, true, true>(s, a);
       return launch_stream_l<ST, W, false, true>(s, a);
     }
   }
