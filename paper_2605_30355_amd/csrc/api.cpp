@@ -252,6 +252,14 @@ int choose_shape(cosm_state *s) {
         if (int rc = rstream_schedule_for(*s, chosen, p.threads_per_wg, &s->lds)) return rc;
         sh.threads = s->lds.nth;
         sh.lds_bytes = (int32_t)rstream_lds_bytes(s->lds, chosen, s->C);
+      } else if (dual_form_default(*s, chosen, sh.blocks, device_cu_count())) {
+        LdsSchedule L;
+        if (int rc = dual_schedule_for(*s, chosen, &L)) return rc;
+        if (p.threads_per_wg == 0 || p.threads_per_wg == L.nth) {
+          s->lds = std::move(L);
+          sh.threads = s->lds.nth;
+          sh.lds_bytes = (int32_t)dual_lds_bytes(s->lds.n_rows, chosen);
+        }
       }
     }
   }
@@ -779,6 +787,9 @@ int cosm_set_phases(cosm_state *s, int32_t unit, const double *in, int64_t t) {
   if (!rc) {
     s->t = t;
     s->on_grid = on_grid;
+    // the two-class form decides an edge's sign once at either end, which agrees
+    // for differences that are exact: on the grid
+    if (!on_grid && s->lds.dual && s->p.storage == COSM_STORE_FP32) rc = use_pair_shape(s);
   }
   return rc;
 }

@@ -51,7 +51,7 @@ Key make_key(const cosm_state &s) {
   }
   const int32_t variant = (s.sched.grid ? 1 : 0) |
                           (s.sched.dwt_period > 0 && wrap_drift_turns(s) < 0.5 ? 2 : 0) |
-                          (wrap_at_twists(s) ? 4 : 0);
+                          (wrap_at_twists(s) ? 4 : 0) | (wrap_at_sweeps(s) ? 8 : 0);
   return Key{s.n, s.m, s.C, s.R, s.p.storage, s.p.lds_form, s.has_h ? 1 : 0, variant, h};
 }
 
@@ -59,6 +59,8 @@ Key make_key(const cosm_state &s) {
 // K > 0: the register form with K rows; K = kShapeRStream: the streamed
 // register-owner form; 0: the pair form.
 constexpr int32_t kShapeRStream = -1;
+// K = kShapeDual: the two-class form.
+constexpr int32_t kShapeDual = -2;
 
 int apply_shape(cosm_state *s, int32_t W, int32_t nth, int32_t pw, int32_t K,
                 int32_t classic = 0) {
@@ -66,6 +68,8 @@ int apply_shape(cosm_state *s, int32_t W, int32_t nth, int32_t pw, int32_t K,
     if (int rc = reg_schedule_for(*s, W, K, nth, &s->lds)) return rc;
   } else if (K == kShapeRStream) {
     if (int rc = rstream_schedule_for(*s, W, nth, &s->lds)) return rc;
+  } else if (K == kShapeDual) {
+    if (int rc = dual_schedule_for(*s, W, &s->lds)) return rc;
   } else {
     if (int rc = build_lds_schedule(*s, W, nth, &s->lds, true, classic == 0)) return rc;
   }
@@ -73,12 +77,18 @@ int apply_shape(cosm_state *s, int32_t W, int32_t nth, int32_t pw, int32_t K,
   s->shape.rw = W * pw;
   s->shape.blocks = (s->R + s->shape.rw - 1) / s->shape.rw;
   s->shape.lds_bytes = (int32_t)(K == kShapeRStream ? rstream_lds_bytes(s->lds, W, s->C)
+                                 : K == kShapeDual ? dual_lds_bytes(s->lds.n_rows, W)
                                  : lds_sweep_bytes(K > 0 ? s->lds.n_rows : s->n_slots, W, s->C));
   s->shape.threads = s->lds.nth;
   return upload_lds_schedule(s);
 }
 
 }  // namespace
+
+int use_pair_shape(cosm_state *s) {
+  const int32_t pw = (s->p.storage == COSM_STORE_FP32 || s->p.storage == COSM_STORE_FIX32) ? 1 : 2;
+  return apply_shape(s, s->shape.rw / pw, 0, pw, 0);
+}
 
 int upload_lds_schedule(cosm_state *s) {
   const LdsSchedule &L = s->lds;
@@ -93,6 +103,14 @@ int upload_lds_schedule(cosm_state *s) {
                                   L.slot_vertex.size() * 4, hipMemcpyHostToDevice, s->stream));
     COSM_HIP_CHECK(hipMemcpyAsync(s->d.reg_vertex, L.reg_vertex.data(), L.reg_vertex.size() * 4,
                                   hipMemcpyHostToDevice, s->stream));
+    COSM_HIP_CHECK(hipStreamSynchronize(s->stream));  // host vectors may change next
+    return COSM_OK;
+  }
+  if (L.dual) {
+    COSM_HIP_CHECK(hipMemcpyAsync(s->d.rs_words, L.dual_words.data(), L.dual_words.size() * 4,
+                                  hipMemcpyHostToDevice, s->stream));
+    COSM_HIP_CHECK(hipMemcpyAsync(s->d.slot_vertex, L.slot_vertex.data(),
+                                  L.slot_vertex.size() * 4, hipMemcpyHostToDevice, s->stream));
     COSM_HIP_CHECK(hipStreamSynchronize(s->stream));  // host vectors may change next
     return COSM_OK;
   }
@@ -221,6 +239,8 @@ int autotune_lds_shape(cosm_state *s, const std::vector<int32_t> &widths) {
     for (int32_t W : widths)
       for (int32_t req : {0, 512, 768, 1024})
         for (int32_t classic : {0, 1}) cands.emplace_back(W, req, 0, classic);
+  if (form == COSM_LDS_FORM_AUTO || form == COSM_LDS_FORM_PAIR)
+    for (int32_t W : widths) cands.emplace_back(W, 0, kShapeDual, 0);
   if ((form == COSM_LDS_FORM_AUTO || form == COSM_LDS_FORM_REGISTER) && reg_form_supported(*s))
     for (int32_t W : widths)
       for (int32_t K : {1, 2, 4}) cands.emplace_back(W, 0, K, 0);
@@ -235,6 +255,7 @@ int autotune_lds_shape(cosm_state *s, const std::vector<int32_t> &widths) {
     const int32_t W = std::get<0>(cand), req = std::get<1>(cand), K = std::get<2>(cand);
     const int32_t classic = std::get<3>(cand);
     if (K == 0 && req > 0 && req < auto_nth / 2) continue;  // far too few threads for one pass
+    if (K == kShapeDual && !dual_form_supported(*s, W)) continue;
     rc = apply_shape(s, W, req, pw, K, classic);
     if (rc && K != 0) {  // a register form does not apply to this shape
       rc = COSM_OK;

@@ -154,6 +154,10 @@ struct LdsSchedule {
   std::vector<uint32_t> rs_words;
   std::vector<uint32_t> rs_pwords;
   std::vector<uint32_t> rs_act;
+  // Two-class form (dual = true; small graphs): per round of two classes and
+  // thread kDualWords words (sweep_dual.hip); rows are the vertices in order.
+  bool dual = false;
+  std::vector<uint32_t> dual_words;  // [rounds][kDualWords][nth]
   int32_t reg_k = 0;
   int32_t reg_free = 0;
   std::vector<int32_t> reg_vertex;
@@ -161,6 +165,8 @@ struct LdsSchedule {
   int64_t reg_edges = 0;        // edges with an endpoint in registers
   int64_t reg_conflicts = 0;    // lane groups whose rows share a bank (extra LDS cycles)
 };
+constexpr int32_t kDualWords = 6;
+constexpr int32_t kDualVerticesMax = 1024;
 constexpr int32_t kRegKMax = 4;
 // Streamed register-owner form: register rows per thread (one of 8, 12, 16),
 // pair slots per class, classes.
@@ -305,6 +311,8 @@ double wrap_drift_turns(const cosm_state &s);
 // (kernels.hip).  Wider than lds_lazy_wrap's half turn, which also bounds the
 // forms without the parity step and is what cosm_info.lazy_wrap reports.
 bool wrap_at_twists(const cosm_state &s);
+// The same bound for a wrap at the end of every sweep.
+bool wrap_at_sweeps(const cosm_state &s);
 int launch_readout(cosm_state *s);
 // Optimal-bisector readout (readout_opt.hip); h must be absent.
 int launch_readout_optimal(cosm_state *s);
@@ -325,6 +333,14 @@ int build_lds_schedule(const cosm_state &s, int32_t W, int32_t nth_request, LdsS
 // The streamed word form's sweep (sweep_stream.hip), for states whose schedule
 // has it (lds.stream).
 int launch_sweeps_stream(cosm_state *s, int64_t n_sweeps);
+// Two-class form (sweep_dual.hip; small graphs): its schedule for rows of W
+// words, or COSM_ERANGE where it does not apply, and its LDS bytes.
+bool dual_form_supported(const cosm_state &s, int32_t W);
+// Untimed choice: the two-class form where every workgroup has a CU to itself,
+// so that latency and not throughput is what it waits for.
+bool dual_form_default(const cosm_state &s, int32_t W, int32_t blocks, int32_t cus);
+int dual_schedule_for(const cosm_state &s, int32_t W, LdsSchedule *out);
+size_t dual_lds_bytes(int32_t n_rows, int W);
 // Register-owner schedule (see LdsSchedule) for rows of W words, K register
 // vertices per thread and nth_request threads (0: as many as the register
 // vertices need).  COSM_ERANGE when the form does not apply (more than
@@ -353,6 +369,9 @@ int pick_reg_schedule(cosm_state *s, int32_t W, int32_t nth);
 int rstream_schedule_for(const cosm_state &s, int32_t W, int32_t nth, LdsSchedule *out);
 // Measure candidate LDS shapes (row widths in words) and keep the fastest.
 int autotune_lds_shape(cosm_state *s, const std::vector<int32_t> &widths);
+// Puts the state into the pair layout at its row width (for FP32 phases off the
+// grid, which the two-class form's one-sided updates need).
+int use_pair_shape(cosm_state *s);
 // Uploads the bias field in LDS-slot order (no-op without bias fields).
 int upload_h_slot(cosm_state *s);
 // Uploads s->lds (the schedule in the kernel's encoding, the slots per class,

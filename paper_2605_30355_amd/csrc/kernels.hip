@@ -72,24 +72,10 @@ __global__ void __launch_bounds__(1024) k_sweep_lds(const LdsArgs a) {
   const int32_t r0 = xcd_block(blockIdx.x, gridDim.x) * RW;
   const int32_t nvalid = min(RW, a.R - r0);
 
-  // HBM [n][R] -> LDS rows
-  for (int s = tid; s < a.n_rows; s += nth) {
-    const size_t base = (size_t)a.slot_vertex[s] * a.R + r0;
-    float v[RW];
-#pragma unroll
-    for (int k = 0; k < RW; k++) v[k] = (k < nvalid) ? F::load_elem(a.phases, base + k) : 0.0f;
-    uint32_t w[W];
-    F::template pack<W>(v, w);
-    lds_store<W>(lds, s, w);
-  }
-
-  // dummy rows for masked lanes (zero, never stored back), the table of
-  // reference angles (filled at the first twist of every chunk), then the slots
-  // per class
-  for (int s = tid; s < kDummyRows; s += nth) {
-    const uint32_t z[W] = {};
-    lds_store<W>(lds, a.n_rows + s, z);
-  }
+  // HBM [n][R] -> LDS rows; dummy rows for masked lanes (zero, never stored
+  // back), the table of reference angles (filled at the first twist of every
+  // chunk), then the slots per class
+  lds_rows_in<ST, W>(lds, a, r0, nvalid, nth);
   float *theta_buf = reinterpret_cast<float *>(lds + (size_t)(a.n_rows + kDummyRows) * W);  // [kThetaChunk][RW]
   float *dir_buf = theta_buf + kThetaFloats;                                  // [kThetaChunk][RW]
   int32_t *Ks = reinterpret_cast<int32_t *>(dir_buf + kThetaFloats);          // [C]
@@ -251,27 +237,7 @@ __global__ void __launch_bounds__(1024) k_sweep_lds(const LdsArgs a) {
     // Bias fields: one more conflict-free sub-sweep against the virtual spin
     // at phase 0, after the classes (rows are final after the last barrier).
     if (!FUSE && a.h_slot != nullptr) {
-      for (int s0 = tid; s0 < a.n_rows; s0 += 4 * nth) {
-        int32_t hv[4];
-        uint32_t w[4][W];
-#pragma unroll
-        for (int q = 0; q < 4; q++) {
-          hv[q] = s0 + q * nth < a.n_rows ? a.h_slot[s0 + q * nth] : 0;
-          if (hv[q] != 0) lds_load<W>(lds, s0 + q * nth, w[q]);
-        }
-#pragma unroll
-        for (int q = 0; q < 4; q++) {
-          if (hv[q] != 0) {
-            float v[RW];
-            F::template unpack<W>(w[q], v);
-            const float ah = alpha * (float)hv[q];
-#pragma unroll
-            for (int k = 0; k < RW; k++) field_update<ST, LAZY>(v[k], ah);
-            F::template pack<W>(v, w[q]);
-            lds_store<W>(lds, s0 + q * nth, w[q]);
-          }
-        }
-      }
+      field_pass<ST, W, LAZY>(lds, a, alpha, nth);
       __syncthreads();
     }
     // Dual window twist every `period` sweeps, on the phases after the last
@@ -296,40 +262,13 @@ __global__ void __launch_bounds__(1024) k_sweep_lds(const LdsArgs a) {
       }
       TwistOps<ST, W> op;
       op.set(cth, tws, sc.win2);
-      // four rows per thread in flight: all loads, then the updates and stores
-      for (int s0 = tid; s0 < a.n_rows; s0 += 4 * nth) {
-        uint32_t w[4][W];
-#pragma unroll
-        for (int q = 0; q < 4; q++)
-          if (s0 + q * nth < a.n_rows) lds_load<W>(lds, s0 + q * nth, w[q]);
-#pragma unroll
-        for (int q = 0; q < 4; q++) {
-          if (s0 + q * nth < a.n_rows) {
-            twist_row<ST, W, LAZY>(op, w[q]);
-            lds_store<W>(lds, s0 + q * nth, w[q]);
-          }
-        }
-      }
+      twist_pass<ST, W, LAZY>(lds, a.n_rows, op, nth);
       __syncthreads();
     }
   }
   if constexpr (RD) f32_round_nearest();
 
-  // LDS rows -> HBM.  16-bit float phases wrapped at the twists only go back
-  // as they are (|y| < 1, within the drift bound): wrapping them here would
-  // change how later steps round them, and with it the trajectory whenever a
-  // trial is split over several calls
-  for (int s = tid; s < a.n_rows; s += nth) {
-    const size_t base = (size_t)a.slot_vertex[s] * a.R + r0;
-    uint32_t w[W];
-    lds_load<W>(lds, s, w);
-    float v[RW];
-    F::template unpack<W>(w, v);
-#pragma unroll
-    for (int k = 0; k < RW; k++)
-      if (k < nvalid)  // (FP32 wraps exactly)
-        F::store_elem(a.phases, base + k, LAZY && ST == COSM_STORE_FP32 ? F::wrap(v[k]) : v[k]);
-  }
+  lds_rows_out<ST, W, LAZY>(lds, a, r0, nvalid, nth);
 }
 
 // ---------------------------------------------------------------------------
@@ -651,6 +590,7 @@ int launch_lds(cosm_state *s, const LdsArgs &a) {
 template <int ST, int W>
 int launch_lds_w(cosm_state *s, const LdsArgs &a) {
   if (s->lds.reg_k > 0) return launch_sweeps_reg(s, a, W);
+  if (s->lds.dual) return launch_sweeps_dual(s, a, W);
   const int slots = a.total_slots;
   // one slot per class and exactly 4 / 8 slots: the unconditional form
   const bool one_each = slots == a.C && slots <= 32 && a.bar_mask == (uint32_t)((1ull << slots) - 1);
@@ -683,7 +623,7 @@ int sweeps_lds_st(cosm_state *s, int64_t n_sweeps) {
   uint32_t mask = 0;
   {
     int j = 0;
-    for (int c = 0; c < s->C; c++) {
+    for (int c = 0; c < (int)s->lds.K.size(); c++) {
       j += s->lds.K[(size_t)c];
       if (s->lds.K[(size_t)c] > 0 && j - 1 < 32) mask |= 1u << (j - 1);
     }
@@ -692,6 +632,7 @@ int sweeps_lds_st(cosm_state *s, int64_t n_sweeps) {
   a.fuse_k = s->lds.fuse_k;
   a.reg_vertex = s->d.reg_vertex;
   a.reg_free = s->lds.reg_free;
+  a.dual = s->d.rs_words;
   a.sch = make_sweep_schedule(s->sched, s->t);
   a.k0 = (uint32_t)(s->seed & 0xffffffffu);
   a.k1 = (uint32_t)(s->seed >> 32);
@@ -900,6 +841,7 @@ bool lds_twist_fused(const cosm_state &s) {
   // (the streamed word form runs its twist as a pass: measured faster than
   // the fused twist there, whose extra arithmetic lengthens the last class)
   if (s.lds.stream) return false;
+  if (s.lds.dual) return true;
   if (s.lds.reg_k > 0) return s.C == 4;
   if (s.has_h) return false;
   const int slots = s.lds.total_slots;
@@ -909,16 +851,23 @@ bool lds_twist_fused(const cosm_state &s) {
   return slots > kRegisterSlotsMax;
 }
 
+namespace {
+// The largest step and twist in turns (grid: exact products of small integers
+// and powers of two).
+double alpha_max_turns(const Schedule &sc) {
+  return sc.grid ? (double)sc.a0_units * (double)sc.aunit : (double)sc.alpha0_turns;
+}
+double twist_max_turns(const Schedule &sc) {
+  return sc.grid ? (double)sc.twist_num2 * (double)sc.a0_units * (double)sc.tunit
+                 : (double)sc.dwt_ratio * alpha_max_turns(sc);
+}
+}  // namespace
+
 double wrap_drift_turns(const cosm_state &s) {
-  // the largest step and the largest twist in turns (grid: exact products of
-  // small integers and powers of two), then the largest drift of one phase
-  // from its wrapped range between two twists: the twist left unwrapped plus
-  // every step of `period` sweeps, J and h alike
-  const Schedule &sc = s.sched;
-  const double alpha_max = sc.grid ? (double)sc.a0_units * (double)sc.aunit : (double)sc.alpha0_turns;
-  const double twist_max = sc.grid ? (double)sc.twist_num2 * (double)sc.a0_units * (double)sc.tunit
-                                   : (double)sc.dwt_ratio * alpha_max;
-  return twist_max + (double)sc.dwt_period * alpha_max * (double)s.wdeg_max;
+  // the largest drift of one phase from its wrapped range between two twists:
+  // the twist left unwrapped plus every step of `period` sweeps, J and h alike
+  return twist_max_turns(s.sched) +
+         (double)s.sched.dwt_period * alpha_max_turns(s.sched) * (double)s.wdeg_max;
 }
 
 bool exact_grid_fp32(const cosm_state &s) {
@@ -940,6 +889,12 @@ bool exact_grid_fp32(const cosm_state &s) {
 // 42.0 -> 41.0 ms (LDS).
 bool wrap_at_twists(const cosm_state &s) {
   return exact_grid_fp32(s) && s.on_grid && s.sched.dwt_period > 0 && wrap_drift_turns(s) < 1.0;
+}
+
+// The same with a wrap at the end of every sweep.
+bool wrap_at_sweeps(const cosm_state &s) {
+  return exact_grid_fp32(s) && s.on_grid &&
+         twist_max_turns(s.sched) + alpha_max_turns(s.sched) * (double)s.wdeg_max < 1.0;
 }
 
 bool grid_parity_step(const cosm_state &s) {

@@ -29,7 +29,125 @@ struct LdsArgs {
   // edges between two LDS rows is in use
   const int32_t *reg_vertex;
   int32_t reg_free;
+  const uint32_t *dual;       // two-class form: its entries
 };
+
+namespace {
+
+// HBM [n][R] -> the LDS rows of the workgroup's replicas, dummy rows zero.
+template <int ST, int W>
+__device__ __forceinline__ void lds_rows_in(uint32_t *lds, const LdsArgs &a, int32_t r0,
+                                            int32_t nvalid, int nth) {
+  using F = Fmt<ST>;
+  constexpr int RW = W * F::kPerWord;
+  for (int s = threadIdx.x; s < a.n_rows; s += nth) {
+    const size_t base = (size_t)a.slot_vertex[s] * a.R + r0;
+    float v[RW];
+#pragma unroll
+    for (int k = 0; k < RW; k++) v[k] = (k < nvalid) ? F::load_elem(a.phases, base + k) : 0.0f;
+    uint32_t w[W];
+    F::template pack<W>(v, w);
+    lds_store<W>(lds, s, w);
+  }
+  for (int s = threadIdx.x; s < kDummyRows; s += nth) {
+    const uint32_t z[W] = {};
+    lds_store<W>(lds, a.n_rows + s, z);
+  }
+}
+
+// LDS rows -> HBM.  16-bit float phases wrapped at the twists only go back as
+// they are (|y| < 1, within the drift bound): wrapping them here would change
+// how later steps round them, and with it the trajectory whenever a trial is
+// split over several calls.  FP32 wraps exactly.
+template <int ST, int W, bool LAZY>
+__device__ __forceinline__ void lds_rows_out(uint32_t *lds, const LdsArgs &a, int32_t r0,
+                                             int32_t nvalid, int nth) {
+  using F = Fmt<ST>;
+  constexpr int RW = W * F::kPerWord;
+  for (int s = threadIdx.x; s < a.n_rows; s += nth) {
+    const size_t base = (size_t)a.slot_vertex[s] * a.R + r0;
+    uint32_t w[W];
+    lds_load<W>(lds, s, w);
+    float v[RW];
+    F::template unpack<W>(w, v);
+#pragma unroll
+    for (int k = 0; k < RW; k++)
+      if (k < nvalid)
+        F::store_elem(a.phases, base + k, LAZY && ST == COSM_STORE_FP32 ? F::wrap(v[k]) : v[k]);
+  }
+}
+
+// Bias fields: one more conflict-free sub-sweep against the virtual spin at
+// phase 0, four rows per thread in flight.
+template <int ST, int W, bool LAZY>
+__device__ __forceinline__ void field_pass(uint32_t *lds, const LdsArgs &a, float alpha, int nth) {
+  using F = Fmt<ST>;
+  constexpr int RW = W * F::kPerWord;
+  for (int s0 = threadIdx.x; s0 < a.n_rows; s0 += 4 * nth) {
+    int32_t hv[4];
+    uint32_t w[4][W];
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      hv[q] = s0 + q * nth < a.n_rows ? a.h_slot[s0 + q * nth] : 0;
+      if (hv[q] != 0) lds_load<W>(lds, s0 + q * nth, w[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      if (hv[q] != 0) {
+        float v[RW];
+        F::template unpack<W>(w[q], v);
+        const float ah = alpha * (float)hv[q];
+#pragma unroll
+        for (int k = 0; k < RW; k++) field_update<ST, LAZY>(v[k], ah);
+        F::template pack<W>(v, w[q]);
+        lds_store<W>(lds, s0 + q * nth, w[q]);
+      }
+    }
+  }
+}
+
+// The twist as a pass of its own: four rows per thread in flight, all loads,
+// then the updates and stores.
+template <int ST, int W, bool LAZY>
+__device__ __forceinline__ void twist_pass(uint32_t *lds, int32_t n_rows, const TwistOps<ST, W> &op,
+                                           int nth) {
+  for (int s0 = threadIdx.x; s0 < n_rows; s0 += 4 * nth) {
+    uint32_t w[4][W];
+#pragma unroll
+    for (int q = 0; q < 4; q++)
+      if (s0 + q * nth < n_rows) lds_load<W>(lds, s0 + q * nth, w[q]);
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      if (s0 + q * nth < n_rows) {
+        twist_row<ST, W, LAZY>(op, w[q]);
+        lds_store<W>(lds, s0 + q * nth, w[q]);
+      }
+    }
+  }
+}
+
+// Compile-time loop indices and flags for the unrolled class loops.
+template <int V>
+struct IntC {
+  static constexpr int value = V;
+};
+template <bool V>
+struct BoolC {
+  static constexpr bool value = V;
+};
+// fn(IntC<0>), ..., fn(IntC<N - 1>)
+template <int N, int I = 0, typename Fn>
+__device__ __forceinline__ void unroll(Fn &&fn) {
+  if constexpr (I < N) {
+    fn(IntC<I>{});
+    unroll<N, I + 1>(fn);
+  }
+}
+
+}  // namespace
+
+// The two-class form's sweeps (sweep_dual.hip).
+int launch_sweeps_dual(cosm_state *s, const LdsArgs &a, int W);
 
 // The register-owner form's sweeps for the state's storage and W words per
 // row (sweep_reg.hip); COSM_EINVAL for a storage, register count or class

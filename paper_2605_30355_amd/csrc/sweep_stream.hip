@@ -61,7 +61,8 @@ struct StreamArgs {
 // only when the phases provably stay there: a twist wraps every row and adds
 // at most twist_max, and until the next one a phase moves by at most
 // period * alpha_max * (largest sum of |J| at one vertex), with the two
-// together below 1/2 turn.
+// together below 1/2 turn -- or below one turn under the parity step, whose sign
+// needs the phases exact but not the difference (wrap_at_twists).
 // FP16 / BF16 / FP16_PK (centred values y = x - 1/2) use the same form to save the two
 // wraps y - rint(y) of every update: no exactness is claimed there, and a
 // value that has drifted to |y| in [1/2, 1) is stored with one bit less of
