@@ -204,6 +204,10 @@ int choose_shape(cosm_state *s) {
   if (p.update == COSM_UPDATE_FULL_GRADIENT) {
     if (p.residency == COSM_RES_LDS || p.residency == COSM_RES_PLAIN)
       return set_error(COSM_ERANGE, "the full-gradient update runs in the HBM form only");
+    if (p.residency == COSM_RES_AUTO &&
+        full_shape(*s, device_cu_count(), &s->lds, &s->shape) == COSM_OK)
+      return COSM_OK;
+    clear_error();
     sh.residency = COSM_RES_HBM;
   }
   const int pw = per_word(p.storage);

@@ -106,9 +106,13 @@ int upload_lds_schedule(cosm_state *s) {
     COSM_HIP_CHECK(hipStreamSynchronize(s->stream));  // host vectors may change next
     return COSM_OK;
   }
-  if (L.dual) {
+  if (L.dual || L.full) {
     COSM_HIP_CHECK(hipMemcpyAsync(s->d.rs_words, L.dual_words.data(), L.dual_words.size() * 4,
                                   hipMemcpyHostToDevice, s->stream));
+    if (L.full)
+      COSM_HIP_CHECK(hipMemcpyAsync(s->d.reg_vertex, L.K.data(), L.K.size() * 4,
+                                    hipMemcpyHostToDevice, s->stream));
+    if (int rc = upload_h_slot(s)) return rc;
     COSM_HIP_CHECK(hipMemcpyAsync(s->d.slot_vertex, L.slot_vertex.data(),
                                   L.slot_vertex.size() * 4, hipMemcpyHostToDevice, s->stream));
     COSM_HIP_CHECK(hipStreamSynchronize(s->stream));  // host vectors may change next

@@ -158,6 +158,10 @@ struct LdsSchedule {
   // thread kDualWords words (sweep_dual.hip); rows are the vertices in order.
   bool dual = false;
   std::vector<uint32_t> dual_words;  // [rounds][kDualWords][nth]
+  // Full-gradient form in LDS (full = true, sweep_full.hip): dual_words holds the
+  // neighbour words [largest degree][n], K the largest degree of each group of
+  // 64 rows; rows in order of falling degree.
+  bool full = false;
   int32_t reg_k = 0;
   int32_t reg_free = 0;
   std::vector<int32_t> reg_vertex;
@@ -167,6 +171,7 @@ struct LdsSchedule {
 };
 constexpr int32_t kDualWords = 6;
 constexpr int32_t kDualVerticesMax = 1024;
+constexpr int32_t kFullDegreeMax = 32;
 constexpr int32_t kRegKMax = 4;
 // Streamed register-owner form: register rows per thread (one of 8, 12, 16),
 // pair slots per class, classes.
@@ -311,8 +316,10 @@ double wrap_drift_turns(const cosm_state &s);
 // (kernels.hip).  Wider than lds_lazy_wrap's half turn, which also bounds the
 // forms without the parity step and is what cosm_info.lazy_wrap reports.
 bool wrap_at_twists(const cosm_state &s);
-// The same bound for a wrap at the end of every sweep.
+// The same bound for a wrap at the end of every sweep, and, for any update, FP32
+// phases on the grid whose drift within one sweep stays below a turn.
 bool wrap_at_sweeps(const cosm_state &s);
+bool grid_drift_below_turn(const cosm_state &s);
 int launch_readout(cosm_state *s);
 // Optimal-bisector readout (readout_opt.hip); h must be absent.
 int launch_readout_optimal(cosm_state *s);
@@ -341,6 +348,9 @@ bool dual_form_supported(const cosm_state &s, int32_t W);
 bool dual_form_default(const cosm_state &s, int32_t W, int32_t blocks, int32_t cus);
 int dual_schedule_for(const cosm_state &s, int32_t W, LdsSchedule *out);
 size_t dual_lds_bytes(int32_t n_rows, int W);
+// Full-gradient update with the phases in LDS (sweep_full.hip): schedule and
+// shape, or COSM_ERANGE where it does not apply.
+int full_shape(const cosm_state &s, int32_t cus, LdsSchedule *out, KernelShape *shape);
 // Register-owner schedule (see LdsSchedule) for rows of W words, K register
 // vertices per thread and nth_request threads (0: as many as the register
 // vertices need).  COSM_ERANGE when the form does not apply (more than

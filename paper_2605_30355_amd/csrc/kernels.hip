@@ -623,7 +623,7 @@ int sweeps_lds_st(cosm_state *s, int64_t n_sweeps) {
   uint32_t mask = 0;
   {
     int j = 0;
-    for (int c = 0; c < (int)s->lds.K.size(); c++) {
+    for (int c = 0; c < s->C && c < (int)s->lds.K.size(); c++) {
       j += s->lds.K[(size_t)c];
       if (s->lds.K[(size_t)c] > 0 && j - 1 < 32) mask |= 1u << (j - 1);
     }
@@ -637,6 +637,7 @@ int sweeps_lds_st(cosm_state *s, int64_t n_sweeps) {
   a.k0 = (uint32_t)(s->seed & 0xffffffffu);
   a.k1 = (uint32_t)(s->seed >> 32);
   a.rid0 = (uint32_t)s->rid0;
+  if (s->lds.full) return launch_sweeps_full(s, a);
   const int W = s->shape.rw / Fmt<ST>::kPerWord;
   if (W == 4) return launch_lds_w<ST, 4>(s, a);
   if (W == 2) return launch_lds_w<ST, 2>(s, a);
@@ -841,7 +842,7 @@ bool lds_twist_fused(const cosm_state &s) {
   // (the streamed word form runs its twist as a pass: measured faster than
   // the fused twist there, whose extra arithmetic lengthens the last class)
   if (s.lds.stream) return false;
-  if (s.lds.dual) return true;
+  if (s.lds.dual || s.lds.full) return true;
   if (s.lds.reg_k > 0) return s.C == 4;
   if (s.has_h) return false;
   const int slots = s.lds.total_slots;
@@ -892,10 +893,11 @@ bool wrap_at_twists(const cosm_state &s) {
 }
 
 // The same with a wrap at the end of every sweep.
-bool wrap_at_sweeps(const cosm_state &s) {
-  return exact_grid_fp32(s) && s.on_grid &&
+bool grid_drift_below_turn(const cosm_state &s) {
+  return s.p.storage == COSM_STORE_FP32 && s.sched.grid && s.on_grid &&
          twist_max_turns(s.sched) + alpha_max_turns(s.sched) * (double)s.wdeg_max < 1.0;
 }
+bool wrap_at_sweeps(const cosm_state &s) { return exact_grid_fp32(s) && grid_drift_below_turn(s); }
 
 bool grid_parity_step(const cosm_state &s) {
   const int32_t st = s.p.storage;

@@ -149,6 +149,9 @@ __device__ __forceinline__ void unroll(Fn &&fn) {
 // The two-class form's sweeps (sweep_dual.hip).
 int launch_sweeps_dual(cosm_state *s, const LdsArgs &a, int W);
 
+// The full-gradient sweeps in LDS (sweep_full.hip).
+int launch_sweeps_full(cosm_state *s, const LdsArgs &a);
+
 // The register-owner form's sweeps for the state's storage and W words per
 // row (sweep_reg.hip); COSM_EINVAL for a storage, register count or class
 // count that has no kernel.
