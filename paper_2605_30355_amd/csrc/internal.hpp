@@ -351,6 +351,8 @@ size_t dual_lds_bytes(int32_t n_rows, int W);
 // Full-gradient update with the phases in LDS (sweep_full.hip): schedule and
 // shape, or COSM_ERANGE where it does not apply.
 int full_shape(const cosm_state &s, int32_t cus, LdsSchedule *out, KernelShape *shape);
+// Whether a state with bias fields runs them and the twist inside the last class.
+bool fields_fused(const cosm_state &s);
 // Register-owner schedule (see LdsSchedule) for rows of W words, K register
 // vertices per thread and nth_request threads (0: as many as the register
 // vertices need).  COSM_ERANGE when the form does not apply (more than

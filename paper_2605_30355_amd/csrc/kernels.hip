@@ -591,6 +591,7 @@ template <int ST, int W>
 int launch_lds_w(cosm_state *s, const LdsArgs &a) {
   if (s->lds.reg_k > 0) return launch_sweeps_reg(s, a, W);
   if (s->lds.dual) return launch_sweeps_dual(s, a, W);
+  if (fields_fused(*s)) return launch_sweeps_fields(s, a, W);
   const int slots = a.total_slots;
   // one slot per class and exactly 4 / 8 slots: the unconditional form
   const bool one_each = slots == a.C && slots <= 32 && a.bar_mask == (uint32_t)((1ull << slots) - 1);
@@ -844,7 +845,7 @@ bool lds_twist_fused(const cosm_state &s) {
   if (s.lds.stream) return false;
   if (s.lds.dual || s.lds.full) return true;
   if (s.lds.reg_k > 0) return s.C == 4;
-  if (s.has_h) return false;
+  if (s.has_h) return fields_fused(s);
   const int slots = s.lds.total_slots;
   bool one_each = slots == s.C;
   for (int32_t k : s.lds.K) one_each = one_each && k == 1;

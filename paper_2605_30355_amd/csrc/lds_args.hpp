@@ -29,7 +29,8 @@ struct LdsArgs {
   // edges between two LDS rows is in use
   const int32_t *reg_vertex;
   int32_t reg_free;
-  const uint32_t *dual;       // two-class form: its entries
+  const uint32_t *dual;       // two-class and full-gradient forms: their entries
+  int32_t last_slot0;         // fused fields: the last class's first slot
 };
 
 namespace {
@@ -151,6 +152,10 @@ int launch_sweeps_dual(cosm_state *s, const LdsArgs &a, int W);
 
 // The full-gradient sweeps in LDS (sweep_full.hip).
 int launch_sweeps_full(cosm_state *s, const LdsArgs &a);
+
+// The sweeps with fields and twist inside the last class (sweep_fields.hip), for
+// states that fields_fused accepts.
+int launch_sweeps_fields(cosm_state *s, const LdsArgs &a, int W);
 
 // The register-owner form's sweeps for the state's storage and W words per
 // row (sweep_reg.hip); COSM_EINVAL for a storage, register count or class
