@@ -253,7 +253,18 @@ int choose_shape(cosm_state *s) {
         sh.threads = s->lds.nth;
         sh.lds_bytes = (int32_t)lds_sweep_bytes(s->lds.n_rows, chosen, s->C);
       } else if (p.lds_form == COSM_LDS_FORM_REGISTER_STREAM) {
-        if (int rc = rstream_schedule_for(*s, chosen, p.threads_per_wg, &s->lds)) return rc;
+        // (its rows are about half the vertices: four replicas per workgroup where
+        // they give every CU one, also past the pair layout's room)
+        const int cus = device_cu_count();
+        if (p.replicas_per_wg == 0 && chosen < 4 && (s->R + 3) / 4 >= cus &&
+            rstream_schedule_for(*s, 4, p.threads_per_wg, &s->lds) == COSM_OK) {
+          chosen = 4;
+          sh.rw = chosen * pw;
+          sh.blocks = (s->R + sh.rw - 1) / sh.rw;
+        } else if (int rc = rstream_schedule_for(*s, chosen, p.threads_per_wg, &s->lds)) {
+          return rc;
+        }
+        clear_error();
         sh.threads = s->lds.nth;
         sh.lds_bytes = (int32_t)rstream_lds_bytes(s->lds, chosen, s->C);
       } else if (dual_form_default(*s, chosen, sh.blocks, device_cu_count())) {

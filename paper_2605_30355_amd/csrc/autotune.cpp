@@ -178,15 +178,30 @@ int rstream_schedule_for(const cosm_state &s, int32_t W, int32_t nth, LdsSchedul
       s.p.update != COSM_UPDATE_SCS)
     return set_error(COSM_ERANGE, "the streamed register form needs FP32 storage, at most 32 "
                                   "classes, edges and no bias fields");
-  LdsSchedule L;
-  if (int rc = build_rstream_schedule(s, W, nth, &L)) return rc;
-  if (!rstream_shape_supported(s.p.storage, W, L.reg_k))
+  const size_t cap = (size_t)lds_capacity_bytes();
+  // (before the schedules are built: even with its whole independent set in
+  // registers the rest of the rows must fit)
+  const int32_t K = rstream_register_rows(s, nth > 0 ? nth : 1024);
+  if (!rstream_shape_supported(s.p.storage, W, K))
     return set_error(COSM_ERANGE, "streamed register form: no kernel for this row width and "
                                   "register count");
-  if (rstream_lds_bytes(L, W, s.C) > (size_t)lds_capacity_bytes())
+  const int64_t held = std::min<int64_t>(independent_set_size(s),
+                                         (int64_t)K * (nth > 0 ? nth : 1024));
+  if ((size_t)(s.n - held) * W * 4 > cap)
     return set_error(COSM_ERANGE, "streamed register form: rows do not fit in LDS");
-  *out = std::move(L);
-  return COSM_OK;
+  // the vertices with an edge in a minor class in registers too, else in LDS (141 x
+  // 141 torus, four replicas per workgroup: 10048 rows; without them 10368, and
+  // 10176 is the most that fit)
+  for (bool solo : {true, false}) {
+    LdsSchedule L;
+    const int rc = build_rstream_schedule(s, W, nth, &L, solo);
+    if (rc && !solo) return rc;
+    if (rc || rstream_lds_bytes(L, W, s.C) > cap) continue;
+    clear_error();
+    *out = std::move(L);
+    return COSM_OK;
+  }
+  return set_error(COSM_ERANGE, "streamed register form: rows do not fit in LDS");
 }
 
 // The register form for a fixed row width: the fewest register rows per
@@ -250,8 +265,10 @@ int autotune_lds_shape(cosm_state *s, const std::vector<int32_t> &widths) {
       for (int32_t K : {1, 2, 4}) cands.emplace_back(W, 0, K, 0);
   // (fewer threads hold more register rows each, and may leave room for a
   // second workgroup per CU)
+  // (its LDS rows are about half the vertices, so that it may run wider rows than
+  // the pair layout has room for)
   if (form == COSM_LDS_FORM_AUTO || form == COSM_LDS_FORM_REGISTER_STREAM)
-    for (int32_t W : widths)
+    for (int32_t W : {4, 2})
       for (int32_t req : {1024, 768, 640, 512}) cands.emplace_back(W, req, kShapeRStream, 0);
   std::vector<Shape> tried;
   int32_t auto_nth = 0;

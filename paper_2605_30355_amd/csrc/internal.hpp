@@ -148,7 +148,10 @@ struct LdsSchedule {
   // LDS rows per class (u row offset | J << 18, v row offset; |J| < 2^13),
   // dummy-row pairs with J = 0 where a lane has none; rs_act [C][nth / 64]:
   // per class and wave, bit 0 set in a register class and bit 1 + p when pair
-  // slot p holds an edge in some lane of the wave (a wave skips the others).
+  // slot p holds an edge in some lane of the wave (a wave skips the others), bit
+  // 1 + kRStreamPairs when the solo slot does: the last register row's edge in a
+  // class without register slots, its word (as in rs_words) in the place of the
+  // last pair slot's.
   // Row offsets are below 2^18 bytes.
   bool rstream = false;
   std::vector<uint32_t> rs_words;
@@ -167,6 +170,7 @@ struct LdsSchedule {
   std::vector<int32_t> reg_vertex;
   int64_t reg_set = 0;          // size of the independent set before any cut to K nth
   int64_t reg_edges = 0;        // edges with an endpoint in registers
+  bool reg_all = false;         // every vertex offered to the registers found a place
   int64_t reg_conflicts = 0;    // lane groups whose rows share a bank (extra LDS cycles)
 };
 constexpr int32_t kDualWords = 6;
@@ -178,6 +182,11 @@ constexpr int32_t kRegKMax = 4;
 constexpr int32_t kRStreamKMax = 16;
 constexpr int32_t kRStreamPairs = 4;
 constexpr int32_t kRStreamClassesMax = 32;
+// Its dummy rows (one per bank residue of a lane group) and the twists whose
+// reference angles it draws at a time: as few as it takes, since its rows fill the
+// LDS to the last kilobyte.
+constexpr int32_t kRStreamDummyRows(int32_t W) { return 64 / W; }
+constexpr int kRStreamTheta = 16;
 constexpr int32_t kRegClassesMax = 8;
 constexpr int32_t kRegRowsSlack = 4096;  // slot_vertex capacity beyond n
 constexpr int32_t kRegisterSlotsMax = 16;  // schedules this short stay in registers
@@ -254,6 +263,7 @@ struct cosm_state {
   cosm::Schedule sched{};
   int32_t n_slots = 0;
   int32_t max_class = 0;
+  mutable std::vector<uint8_t> indep;  // independent set of the register forms, once found
   cosm::LdsSchedule lds;  // resolved lane schedule of the LDS form
   std::vector<int32_t> lds_widths;  // row widths (words) that fit, for the autotuner
   bool has_h = false;
@@ -362,8 +372,13 @@ int build_reg_schedule(const cosm_state &s, int32_t W, int32_t K, int32_t nth_re
                        LdsSchedule *out);
 // The streamed register-owner schedule (reg_k = 8, 12 or 16 register rows per
 // thread, the fewest that hold the independent set, at most kRStreamKMax).
+// solo: with register vertices that have an edge in a class without register
+// slots (one more kind of slot there), so that fewer rows need LDS.
 int build_rstream_schedule(const cosm_state &s, int32_t W, int32_t nth_request,
-                           LdsSchedule *out);
+                           LdsSchedule *out, bool solo = false);
+// The register rows per thread it takes at a thread count.
+int32_t rstream_register_rows(const cosm_state &s, int32_t nth);
+int64_t independent_set_size(const cosm_state &s);
 // The LDS bytes of the streamed register-owner sweep for a schedule.
 size_t rstream_lds_bytes(const LdsSchedule &L, int W, int32_t C);
 // Whether the streamed register-owner kernel exists for this storage, row

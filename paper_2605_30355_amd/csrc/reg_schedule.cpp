@@ -225,6 +225,14 @@ void large_independent(int32_t n, const std::vector<std::vector<Adj>> &adj,
   }
 }
 
+// The instance's independent set, found once per state.
+const std::vector<uint8_t> &independent_set(const cosm_state &s,
+                                            const std::vector<std::vector<Adj>> &adj) {
+  if (s.indep.empty())
+    if (!bipartite_side(s.n, adj, &s.indep)) large_independent(s.n, adj, &s.indep);
+  return s.indep;
+}
+
 inline uint64_t bit(int32_t r) { return 1ull << r; }
 
 // Options of one attempt.  pre: every LDS vertex takes residue (its rank among
@@ -237,10 +245,15 @@ inline uint64_t bit(int32_t r) { return 1ull << r; }
 // that vertices with the same pattern share waves and a class leaves the
 // register slots of the rare patterns (the seams of an odd torus) to a few
 // waves.
+// solo (rstream): register vertices with an edge in a class without register
+// slots (a minor class; the seams of an odd torus) are kept, in the last register
+// row, and that edge runs as a register slot of its own in the minor class (solo
+// slot), in place of the class's last pair slot.
 struct RegOptions {
   int32_t W = 0, K = 0, nth_request = 0;
   bool pre = false;
   bool rstream = false;
+  bool solo = false;
 };
 
 // One lane's entry in a register slot: the LDS endpoint's row (or a dummy
@@ -284,9 +297,8 @@ int build_reg_impl(const cosm_state &s, const RegOptions &o, LdsSchedule *out) {
   }
 
   // 1. the register set
-  std::vector<uint8_t> inI;
-  if (!bipartite_side(n, adj, &inI)) large_independent(n, adj, &inI);
-  std::vector<int32_t> cand;
+  std::vector<uint8_t> inI = independent_set(s, adj);
+  std::vector<int32_t> cand, solo;
   for (int32_t v = 0; v < n; v++)
     if (inI[(size_t)v]) cand.push_back(v);
   int32_t nth = o.nth_request;
@@ -328,6 +340,7 @@ int build_reg_impl(const cosm_state &s, const RegOptions &o, LdsSchedule *out) {
         for (const Adj &a : adj[(size_t)v])
           if (!rclass[(size_t)a.cls]) ok = false;
         if (ok) keep.push_back(v);
+        else if (o.solo && (int32_t)solo.size() < nth) solo.push_back(v);
         else inI[(size_t)v] = 0;
       }
       if (keep.size() != cand.size()) changed = true;
@@ -379,11 +392,14 @@ int build_reg_impl(const cosm_state &s, const RegOptions &o, LdsSchedule *out) {
     }
   }
   std::vector<uint8_t> placed((size_t)n, 0);
+  // fills the free lanes of groups [g0, ngroups) from a list of vertices
+  auto pack = [&](const std::vector<int32_t> &cand, int32_t g0) {
   size_t first_open = 0;  // cand[0 .. first_open) are all placed
-  for (int32_t gi = 0; gi < ngroups && first_open < cand.size(); gi++) {
+  for (int32_t gi = g0; gi < ngroups && first_open < cand.size(); gi++) {
     const int32_t k = gi / groups_per_k, tg = gi % groups_per_k;
     for (int32_t p = 0; p < G; p++) {
       const int32_t half = p / H;
+      if (pos_vertex[(size_t)k * nth + tg * G + p] >= 0) continue;
       int32_t chosen = -1;
       int32_t scanned = 0;
       for (size_t i = first_open; i < cand.size() && scanned < 2048; i++) {
@@ -425,10 +441,15 @@ int build_reg_impl(const cosm_state &s, const RegOptions &o, LdsSchedule *out) {
       while (first_open < cand.size() && placed[(size_t)cand[first_open]]) first_open++;
     }
   }
+  };
+  pack(solo, (K - 1) * groups_per_k);
+  pack(cand, 0);
+  cand.insert(cand.end(), solo.begin(), solo.end());
   // register vertices that found no place go back to LDS
   int64_t reg_edges = 0;
+  bool reg_all = true;
   for (int32_t v : cand) {
-    if (!placed[(size_t)v]) inI[(size_t)v] = 0;
+    if (!placed[(size_t)v]) inI[(size_t)v] = 0, reg_all = false;
     else reg_edges += (int64_t)adj[(size_t)v].size();
   }
 
@@ -439,8 +460,13 @@ int build_reg_impl(const cosm_state &s, const RegOptions &o, LdsSchedule *out) {
     if (!inI[(size_t)u] && !inI[(size_t)v]) free_edges[(size_t)s.h_colour[(size_t)k]].push_back((int32_t)k);
   }
   int32_t reg_free = 0;
+  std::vector<uint8_t> solo_class((size_t)C, 0);
+  for (int32_t v : solo)
+    if (placed[(size_t)v])
+      for (const Adj &a : adj[(size_t)v])
+        if (!rclass[(size_t)a.cls]) solo_class[(size_t)a.cls] = 1;
   for (int32_t c = 0; c < C; c++) {
-    if ((int64_t)free_edges[(size_t)c].size() > (int64_t)P * nth)
+    if ((int64_t)free_edges[(size_t)c].size() > (int64_t)(P - solo_class[(size_t)c]) * nth)
       return set_error(COSM_ERANGE, "too many edges outside the register set");
     if (!free_edges[(size_t)c].empty()) reg_free = 1;
   }
@@ -666,6 +692,15 @@ int build_reg_impl(const cosm_state &s, const RegOptions &o, LdsSchedule *out) {
           L.rs_pwords[2 * i + 1] = (uint32_t)d.rv * rowb;
           if (d.J != 0) L.rs_act[(size_t)c * nw + t / 64] |= 2u << ps;
         }
+      // the solo slot: the last register row's word where the last pair slot's was
+      if (solo_class[(size_t)c])
+        for (int32_t t = 0; t < nth; t++) {
+          const RegEntry &d = reg[((size_t)c * K + K - 1) * nth + t];
+          const size_t i = ((size_t)c * P + P - 1) * nth + t;
+          L.rs_pwords[2 * i] = (uint32_t)d.row * rowb | (d.flip ? 0x80000000u : 0u);
+          L.rs_pwords[2 * i + 1] = __builtin_bit_cast(uint32_t, (float)d.J);
+          if (d.J != 0) L.rs_act[(size_t)c * nw + t / 64] |= 2u << P;
+        }
     }
     L.rstream = true;
     L.fuse = false;
@@ -718,6 +753,7 @@ int build_reg_impl(const cosm_state &s, const RegOptions &o, LdsSchedule *out) {
   L.reg_set = set_size;
   L.reg_edges = reg_edges;
   L.reg_conflicts = conflicts;
+  L.reg_all = reg_all;
   L.fuse_k = 0;
   L.dummy_pairs = true;
   *out = std::move(L);
@@ -746,34 +782,46 @@ int build_reg_schedule(const cosm_state &s, int32_t W, int32_t K, int32_t nth_re
   return COSM_OK;
 }
 
+int64_t independent_set_size(const cosm_state &s) {
+  if (s.indep.empty()) {
+    std::vector<std::vector<Adj>> adj((size_t)s.n);
+    for (int64_t k = 0; k < s.m; k++) {
+      adj[(size_t)s.h_eu[(size_t)k]].push_back({s.h_ev[(size_t)k], (int32_t)k, 0});
+      adj[(size_t)s.h_ev[(size_t)k]].push_back({s.h_eu[(size_t)k], (int32_t)k, 0});
+    }
+    independent_set(s, adj);
+  }
+  int64_t set = 0;
+  for (uint8_t b : s.indep) set += b;
+  return set;
+}
+
+int32_t rstream_register_rows(const cosm_state &s, int32_t nth) {
+  const int64_t set = independent_set_size(s);
+  for (int32_t k : {8, 10, 12, 16})
+    if ((int64_t)k * nth >= set) return k;
+  return kRStreamKMax;
+}
+
 int build_rstream_schedule(const cosm_state &s, int32_t W, int32_t nth_request,
-                           LdsSchedule *out) {
+                           LdsSchedule *out, bool solo) {
   // the fewest register rows (8, 10, 12 or 16) that hold the independent set
   // at the thread count asked for (1024 when none is)
   const int32_t nth = nth_request > 0 ? nth_request : 1024;
-  std::vector<std::vector<Adj>> adj((size_t)s.n);
-  for (int64_t k = 0; k < s.m; k++) {
-    adj[(size_t)s.h_eu[(size_t)k]].push_back({s.h_ev[(size_t)k], (int32_t)k, 0});
-    adj[(size_t)s.h_ev[(size_t)k]].push_back({s.h_eu[(size_t)k], (int32_t)k, 0});
-  }
-  std::vector<uint8_t> inI;
-  if (!bipartite_side(s.n, adj, &inI)) large_independent(s.n, adj, &inI);
-  int64_t set = 0;
-  for (uint8_t b : inI) set += b;
-  int32_t K = kRStreamKMax;
-  for (int32_t k : {8, 10, 12, 16})
-    if ((int64_t)k * nth >= set) {
-      K = k;
-      break;
-    }
+  const int32_t K = rstream_register_rows(s, nth);
   RegOptions a, b;
   a.W = b.W = W;
   a.K = b.K = K;
   a.nth_request = b.nth_request = nth;
   a.rstream = b.rstream = true;
+  a.solo = b.solo = solo;
   a.pre = true;
   LdsSchedule la, lb;
   const int ra = build_reg_impl(s, a, &la);
+  if (ra == 0 && la.reg_all && la.reg_conflicts == 0) {  // nothing left to gain
+    *out = std::move(la);
+    return COSM_OK;
+  }
   const int rb = build_reg_impl(s, b, &lb);
   if (ra && rb) return ra;
   clear_error();
@@ -785,9 +833,9 @@ int build_rstream_schedule(const cosm_state &s, int32_t W, int32_t nth_request,
 }
 
 size_t rstream_lds_bytes(const LdsSchedule &L, int W, int32_t C) {
-  // rows and dummy rows, the twist angles of kThetaChunk twists (FP32: W
+  // rows and dummy rows, the twist angles of kRStreamTheta twists (FP32: W
   // replicas per row), the slot masks
-  return (size_t)(L.n_rows + kDummyRows) * W * 4 + (size_t)kThetaChunk * W * 4 +
+  return (size_t)(L.n_rows + kRStreamDummyRows(W)) * W * 4 + (size_t)kRStreamTheta * W * 4 +
          (size_t)C * (L.nth / 64) * 4;
 }
 

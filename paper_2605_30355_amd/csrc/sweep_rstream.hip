@@ -24,6 +24,15 @@
 // left), a pair slot's one class ahead.  A class either runs all K register
 // slots or none, so no register row is updated on one path and not on
 // another, and the compiler keeps every row in one register.
+//
+// Four replicas per row halve the words, decodes and barriers per update of two,
+// and only the rows outside the registers need LDS; the seam vertices are kept in
+// the last register row too, their seam edges as solo slots (one more branch in the
+// seam classes), or the 141 x 141 torus would not fit.  300 sweeps of
+// 4096 replicas: 141 x 141 torus 18.45 ms (streamed pair form, two replicas per
+// row) -> 12.57; 100 x 100 torus, 8 rows per thread on 640 threads 6.51 -> 10 rows
+// on 512 5.77.  What bounds it now is the vector unit: 2.5 lane operations a word
+// beside the update's five.
 #include <hip/hip_runtime.h>
 
 #include "device_common.hpp"
@@ -131,7 +140,7 @@ __global__ void __launch_bounds__(1024) k_sweep_rstream(const RStreamArgs a) {
   const int32_t nvalid = min(RW, a.R - r0);
 
   // HBM [n][R] -> LDS rows (padding rows and dummy rows zero)
-  for (int s = tid; s < a.n_rows + kDummyRows; s += nth) {
+  for (int s = tid; s < a.n_rows + kRStreamDummyRows(W); s += nth) {
     const int32_t v = s < a.n_rows ? a.slot_vertex[s] : -1;
     float x[RW];
 #pragma unroll
@@ -141,10 +150,10 @@ __global__ void __launch_bounds__(1024) k_sweep_rstream(const RStreamArgs a) {
     F::template pack<W>(x, w);
     lds_store<W>(lds, s, w);
   }
-  // the twist angles of kThetaChunk twists (no bias fields: no direction
+  // the twist angles of kRStreamTheta twists (no bias fields: no direction
   // table), then the slot masks
-  float *theta_buf = reinterpret_cast<float *>(lds + (size_t)(a.n_rows + kDummyRows) * W);
-  uint32_t *act = reinterpret_cast<uint32_t *>(theta_buf + kThetaChunk * RW);  // [C][nw]
+  float *theta_buf = reinterpret_cast<float *>(lds + (size_t)(a.n_rows + kRStreamDummyRows(W)) * W);
+  uint32_t *act = reinterpret_cast<uint32_t *>(theta_buf + kRStreamTheta * RW);  // [C][nw]
   for (int i = tid; i < a.C * nw; i += nth) act[i] = a.act[i];
   // HBM -> register rows
   uint32_t own[K][W];
@@ -251,6 +260,15 @@ __global__ void __launch_bounds__(1024) k_sweep_rstream(const RStreamArgs a) {
           update_pair<ST, W, LAZY>(x.u, x.v, x.aJ, pm);
           row_store<W>(x.ou, x.u);
           row_store<W>(x.ov, x.v);
+        } else if (p == P - 1 && ((m >> (1 + P)) & 1u)) {
+          // the solo slot: the last register row's edge in a minor class
+          const uint32_t off = wp[p].x & 0x7fffffffu, fm = wp[p].x & 0x80000000u;
+          const float aJ =
+              __uint_as_float(__float_as_uint(amag * __uint_as_float(wp[p].y)) ^ fm);
+          uint32_t w[W];
+          row_load<W>(off, w);
+          update_owner<ST, W, LAZY>(own[K - 1], w, aJ, fm, pm);
+          row_store<W>(off, w);
         }
         wp[p] = pword(cn, p);
       }
@@ -260,9 +278,9 @@ __global__ void __launch_bounds__(1024) k_sweep_rstream(const RStreamArgs a) {
     // Dual window twist every `period` sweeps, after the last class: the
     // register rows by their owners, the LDS rows by all threads
     if (twist_now) {
-      const int q = (int)(tw % (uint32_t)kThetaChunk);
+      const int q = (int)(tw % (uint32_t)kRStreamTheta);
       if (q == 0) {
-        theta_fill(theta_buf, nullptr, kThetaChunk, RW, t, sc.period, a.rid0 + (uint32_t)r0,
+        theta_fill(theta_buf, nullptr, kRStreamTheta, RW, t, sc.period, a.rid0 + (uint32_t)r0,
                    a.k0, a.k1, sc.win, sc.tshift, sc.tscale);
         __syncthreads();
       }
@@ -339,6 +357,7 @@ int launch_rstream_l(cosm_state *s, const RStreamArgs &a, int W, int K) {
   if (W == 2 && K == 12) return launch_rstream_k<ST, 2, 12, LAZY>(s, a);
   if (W == 2 && K == 16) return launch_rstream_k<ST, 2, 16, LAZY>(s, a);
   if (W == 4 && K == 8) return launch_rstream_k<ST, 4, 8, LAZY>(s, a);
+  if (W == 4 && K == 10) return launch_rstream_k<ST, 4, 10, LAZY>(s, a);
   return set_error(COSM_EINVAL, "streamed register form: unsupported row width or register count");
 }
 
@@ -346,7 +365,7 @@ int launch_rstream_l(cosm_state *s, const RStreamArgs &a, int W, int K) {
 
 bool rstream_shape_supported(int32_t storage, int32_t W, int32_t K) {
   if (storage != COSM_STORE_FP32) return false;
-  return (W == 2 && (K == 8 || K == 10 || K == 12 || K == 16)) || (W == 4 && K == 8);
+  return (W == 2 && (K == 8 || K == 10 || K == 12 || K == 16)) || (W == 4 && (K == 8 || K == 10));
 }
 
 int launch_sweeps_rstream(cosm_state *s, int64_t n_sweeps) {
