@@ -672,11 +672,11 @@ int cosm_energy(cosm_state *s, const int8_t *spins, int8_t *spins_out, int64_t *
   } else {
     if (int rc = launch_readout(s)) return rc;
   }
-  COSM_HIP_CHECK(hipMemcpyAsync(H_out, s->d.H, (size_t)s->R * 8, hipMemcpyDeviceToHost, s->stream));
-  COSM_HIP_CHECK(hipMemcpyAsync(cut_out, s->d.cut, (size_t)s->R * 8, hipMemcpyDeviceToHost, s->stream));
-  if (spins_out != nullptr)
-    COSM_HIP_CHECK(hipMemcpyAsync(spins_out, s->d.spins, nr, hipMemcpyDeviceToHost, s->stream));
-  return sync(s);
+  HostPiece out[kHostPieces] = {{H_out, s->d.H, (size_t)s->R * 8},
+                                {cut_out, s->d.cut, (size_t)s->R * 8},
+                                {spins_out, s->d.spins, nr}};
+  // (a state in the static array allocates nothing)
+  return copy_to_host(s->stream, out, spins_out != nullptr ? 3 : 2, s->static_dev < 0);
 }
 
 int cosm_solve_to_target(cosm_state *s, int64_t target_H, int64_t max_trials,

@@ -885,15 +885,12 @@ int cosm_batch_results(cosm_batch *b, int32_t graph_id, int64_t *H_out, int64_t 
   if (b == nullptr || graph_id < 0 || graph_id >= (int32_t)b->graphs.size())
     return set_error(COSM_EINVAL, "bad graph id");
   const GraphDev &d = b->graphs[(size_t)graph_id]->dev;
-  if (H_out)
-    COSM_HIP_CHECK(hipMemcpyAsync(H_out, d.ro.H, (size_t)d.R * 8, hipMemcpyDeviceToHost, b->stream));
-  if (cut_out)
-    COSM_HIP_CHECK(hipMemcpyAsync(cut_out, d.ro.cut, (size_t)d.R * 8, hipMemcpyDeviceToHost, b->stream));
-  if (spins_out)
-    COSM_HIP_CHECK(hipMemcpyAsync(spins_out, d.ro.spins, (size_t)d.R * d.n, hipMemcpyDeviceToHost,
-                                  b->stream));
-  COSM_HIP_CHECK(hipStreamSynchronize(b->stream));
-  return COSM_OK;
+  HostPiece out[kHostPieces];
+  int count = 0;
+  if (H_out) out[count++] = {H_out, d.ro.H, (size_t)d.R * 8};
+  if (cut_out) out[count++] = {cut_out, d.ro.cut, (size_t)d.R * 8};
+  if (spins_out) out[count++] = {spins_out, d.ro.spins, (size_t)d.R * d.n};
+  return copy_to_host(b->stream, out, count, true);
 }
 
 }  // extern "C"

@@ -296,6 +296,18 @@ int init_state(cosm_state **out, int32_t n, int64_t m, const int32_t *eu, const 
 // Releases the static scratch array of a device held by a state (static_scratch.hip).
 void release_static_scratch(int32_t dev);
 
+// ---- results to the host (host_copy.cpp) -------------------------------------------
+// Copies up to kHostPieces pieces of device memory to the caller's arrays, in
+// stream order, and waits (p is reordered).  may_allocate: pinned memory may be
+// taken from a pool shared by the process (blocks of 8.6 MiB, at most four kept).
+struct HostPiece {
+  void *dst;
+  const void *src;
+  size_t bytes;
+};
+constexpr int kHostPieces = 3;
+int copy_to_host(hipStream_t stream, HostPiece *p, int count, bool may_allocate);
+
 // ---- kernel launchers (kernels.hip) -------------------------------------------------
 int launch_init(cosm_state *s);
 int launch_sweeps(cosm_state *s, int64_t n_sweeps);
