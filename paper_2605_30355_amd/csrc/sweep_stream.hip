@@ -74,6 +74,10 @@ __device__ __forceinline__ void update_words_lazy(uint32_t (&wu)[W], uint32_t (&
     update_words<ST, W, true>(wu, wv, aJ);
     return;
   }
+  if constexpr (ST == COSM_STORE_FP16 && RD) {
+    update_words_mix<W, true>(wu, wv, aJ, pm);
+    return;
+  }
   using F = Fmt<ST>;
   constexpr int RW = W * F::kPerWord;
   float xu[RW], xv[RW];
