@@ -34,7 +34,7 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 struct MemPlan {
   size_t phases, desc, jmag, class_off, slot_vertex, reg_vertex, rs_words, rs_pwords, rs_act, h_slot, eu, ev, J, h, peu, pev, pJ, spins, H, cut, best_p,
       inc_off, inc_nbr, inc_J, phases_alt, opt_keys, opt_keys2, opt_vals, opt_vals2, opt_off,
-      opt_temp, opt_temp_bytes, codes, total;
+      opt_temp, opt_temp_bytes, codes, dual_entries, dual_theta, total;
 };
 
 MemPlan plan_memory(int32_t n, int64_t m, int32_t C, int32_t R, const cosm_params &p) {
@@ -79,7 +79,10 @@ MemPlan plan_memory(int32_t n, int64_t m, int32_t C, int32_t R, const cosm_param
   mp.inc_off = take(fg ? ((size_t)n + 1) * 4 : 0);
   mp.inc_nbr = take(fg ? (size_t)(2 * m) * 4 : 0);
   mp.inc_J = take(fg ? (size_t)(2 * m) * 4 : 0);
-  mp.phases_alt = take(fg ? nr * storage_bytes(p.storage) : 0);
+  const bool dual = dual_hbm_form(n, C, R, p);
+  mp.phases_alt = take(fg || dual ? nr * storage_bytes(p.storage) : 0);
+  mp.dual_entries = take(dual ? dual_hbm_entry_bytes(n, C) : 0);
+  mp.dual_theta = take(dual ? (size_t)R * 4 : 0);
   const bool opt = p.readout == COSM_READOUT_OPTIMAL;
   mp.opt_keys = take(opt ? nr * 4 : 0);
   mp.opt_keys2 = take(opt ? nr * 4 : 0);
@@ -570,6 +573,8 @@ int init_state(cosm_state **out, int32_t n, int64_t m, const int32_t *eu, const 
   d.inc_nbr = at<uint32_t>(s->base, mp.inc_nbr);
   d.inc_J = at<float>(s->base, mp.inc_J);
   d.phases_alt = at<void>(s->base, mp.phases_alt);
+  d.dual_entries = at<void>(s->base, mp.dual_entries);
+  d.dual_theta = at<float>(s->base, mp.dual_theta);
   d.opt_keys = at<uint32_t>(s->base, mp.opt_keys);
   d.opt_keys2 = at<uint32_t>(s->base, mp.opt_keys2);
   d.opt_vals = at<uint32_t>(s->base, mp.opt_vals);
@@ -594,6 +599,8 @@ int init_state(cosm_state **out, int32_t n, int64_t m, const int32_t *eu, const 
   rc = rc ? rc : up(d.peu, peu.data(), (size_t)m * 4);
   rc = rc ? rc : up(d.pev, pev.data(), (size_t)m * 4);
   rc = rc ? rc : up(d.pJ, pJ.data(), (size_t)m * 4);
+  if (s->shape.residency == COSM_RES_HBM && dual_hbm_form(n, num_colours, replicas, s->p))
+    rc = rc ? rc : upload_dual_hbm(s);
   if (s->p.update == COSM_UPDATE_FULL_GRADIENT) {
     rc = rc ? rc : up(d.inc_off, inc_off.data(), inc_off.size() * 4);
     rc = rc ? rc : up(d.inc_nbr, inc_nbr.data(), inc_nbr.size() * 4);

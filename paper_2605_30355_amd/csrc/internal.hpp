@@ -225,7 +225,9 @@ struct DeviceBuffers {
   int32_t *inc_off = nullptr;   // [n+1]
   uint32_t *inc_nbr = nullptr;  // [2m] neighbour | (1u << 31 when the vertex is the edge's u)
   float *inc_J = nullptr;       // [2m]
-  void *phases_alt = nullptr;   // [n][R]
+  void *phases_alt = nullptr;   // [n][R] (also the two-class device-memory form's)
+  void *dual_entries = nullptr; // two-class device-memory form: its entries
+  float *dual_theta = nullptr;  // [R]
   // optimal-bisector readout: sort keys and values [R][n] (twice), segment
   // offsets [R + 1], the sort's temporary storage
   uint32_t *opt_keys = nullptr, *opt_keys2 = nullptr, *opt_vals = nullptr, *opt_vals2 = nullptr;
@@ -281,6 +283,7 @@ struct cosm_state {
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   // device whose static scratch array holds the buffers (cosm_init_static), or -1
   int32_t static_dev = -1;
+  std::vector<int32_t> dual_count;  // two-class device-memory form: entries of each round
 };
 
 namespace cosm {
@@ -342,6 +345,15 @@ bool wrap_at_twists(const cosm_state &s);
 // phases on the grid whose drift within one sweep stays below a turn.
 bool wrap_at_sweeps(const cosm_state &s);
 bool grid_drift_below_turn(const cosm_state &s);
+// Step size and twist of sweep t (1-based) in turns, exactly as the device
+// evaluates them.
+float host_alpha(const Schedule &sc, int64_t t);
+float host_twist(const Schedule &sc, int64_t t);
+// The device-memory forms' field sub-sweep and twist on replicas [rbeg, rbeg +
+// rcount), and the replicas per lane their accesses can take.
+int launch_field_hbm(cosm_state *s, float alpha, int32_t rbeg, int32_t rcount);
+int launch_dwt_hbm(cosm_state *s, int64_t t, int32_t rbeg, int32_t rcount);
+int hbm_vec(int32_t R, int32_t rbeg, int32_t rcount);
 int launch_readout(cosm_state *s);
 // Optimal-bisector readout (readout_opt.hip); h must be absent.
 int launch_readout_optimal(cosm_state *s);
@@ -362,6 +374,23 @@ int build_lds_schedule(const cosm_state &s, int32_t W, int32_t nth_request, LdsS
 // The streamed word form's sweep (sweep_stream.hip), for states whose schedule
 // has it (lds.stream).
 int launch_sweeps_stream(cosm_state *s, int64_t n_sweeps);
+// An entry of the two-class forms (sweep_dual.hip, sweep_dual_hbm.hip): an edge
+// (u, v) of the round's second class (v = -1, J = 0 where a vertex has none) and the
+// first class's edges at u and v (partner -1 for none; f: the endpoint is that
+// edge's v).  A round's entries cover every vertex once.
+struct DualEntry {
+  int32_t u, v, pu, pv;
+  int32_t J, Ju, Jv;
+  int32_t fu, fv;
+};
+std::vector<std::vector<DualEntry>> dual_entries(const cosm_state &s);
+// The device-memory sweeps two classes at a time (sweep_dual_hbm.hip): whether a
+// state of these sizes takes them (it then has a second phase buffer and the
+// entries in device memory), and its launcher.
+bool dual_hbm_form(int32_t n, int32_t C, int32_t R, const cosm_params &p);
+size_t dual_hbm_entry_bytes(int32_t n, int32_t C);
+int upload_dual_hbm(cosm_state *s);
+int launch_sweeps_dual_hbm(cosm_state *s, int64_t n_sweeps);
 // Two-class form (sweep_dual.hip; small graphs): its schedule for rows of W
 // words, or COSM_ERANGE where it does not apply, and its LDS bytes.
 bool dual_form_supported(const cosm_state &s, int32_t W);

@@ -23,10 +23,37 @@
 #include <hip/hip_runtime.h>
 
 #include "device_common.hpp"
+#include "hbm_vec.hpp"
 #include "internal.hpp"
 #include "lds_args.hpp"
 
 namespace cosm {
+
+// Replicas per lane of the HBM kernels: the widest of 4, 2, 1 that keeps every
+// access aligned (R, the first replica and the count all multiples of it).
+int hbm_vec(int32_t R, int32_t rbeg, int32_t rcount) {
+  for (int v : {4, 2})
+    if (R % v == 0 && rbeg % v == 0 && rcount % v == 0) return v;
+  return 1;
+}
+
+// Step size of sweep t (1-based) in turns, exactly as the device evaluates it.
+float host_alpha(const Schedule &sc, int64_t t) {
+  if (sc.grid) {
+    const int64_t q = (sc.a0_units * (sc.S - t + 1) + sc.S / 2) / sc.S;
+    return (float)q * sc.aunit;
+  }
+  return (float)(sc.S - t + 1) * (sc.alpha0_turns / (float)sc.S);
+}
+
+float host_twist(const Schedule &sc, int64_t t) {
+  if (sc.grid) {
+    const int64_t q = (sc.a0_units * (sc.S - t + 1) + sc.S / 2) / sc.S;
+    return (float)(sc.twist_num2 * q) * sc.tunit;
+  }
+  return sc.dwt_ratio * host_alpha(sc, t);
+}
+
 namespace {
 
 
@@ -272,81 +299,6 @@ __global__ void __launch_bounds__(1024) k_sweep_lds(const LdsArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// VEC consecutive replicas of one vertex row in one access (8 or 16 bytes for
-// FP32 and FIX32, 4 or 8 for the 16-bit formats); idx is a multiple of VEC.
-typedef float hbm_f32x2 __attribute__((ext_vector_type(2)));
-typedef float hbm_f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t hbm_u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t hbm_u32x4 __attribute__((ext_vector_type(4)));
-template <typename T>
-using gvec = T __attribute__((address_space(1))) *;
-
-template <int ST, int VEC>
-__device__ __forceinline__ void load_vec(const void *p, size_t idx, float (&x)[VEC]) {
-  using F = Fmt<ST>;
-  if constexpr (VEC == 1) {
-    x[0] = F::load_elem(p, idx);
-  } else if constexpr (ST == COSM_STORE_FP32) {
-    const float *q = static_cast<const float *>(p) + idx;
-    if constexpr (VEC == 4) {
-      const hbm_f32x4 v = *(gvec<const hbm_f32x4>)(q);
-      x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
-    } else {
-      const hbm_f32x2 v = *(gvec<const hbm_f32x2>)(q);
-      x[0] = v.x; x[1] = v.y;
-    }
-  } else if constexpr (ST == COSM_STORE_FIX32) {
-    const uint32_t *q = static_cast<const uint32_t *>(p) + idx;
-    if constexpr (VEC == 4) {
-      const hbm_u32x4 v = *(gvec<const hbm_u32x4>)(q);
-      x[0] = F::dec(v.x); x[1] = F::dec(v.y); x[2] = F::dec(v.z); x[3] = F::dec(v.w);
-    } else {
-      const hbm_u32x2 v = *(gvec<const hbm_u32x2>)(q);
-      x[0] = F::dec(v.x); x[1] = F::dec(v.y);
-    }
-  } else {
-    const uint16_t *q = static_cast<const uint16_t *>(p) + idx;
-    if constexpr (VEC == 4) {
-      const hbm_u32x2 v = *(gvec<const hbm_u32x2>)(q);
-      x[0] = F::dec(v.x & 0xffffu); x[1] = F::dec(v.x >> 16);
-      x[2] = F::dec(v.y & 0xffffu); x[3] = F::dec(v.y >> 16);
-    } else {
-      const uint32_t v = *(gvec<const uint32_t>)(q);
-      x[0] = F::dec(v & 0xffffu); x[1] = F::dec(v >> 16);
-    }
-  }
-}
-template <int ST, int VEC>
-__device__ __forceinline__ void store_vec(void *p, size_t idx, const float (&x)[VEC]) {
-  using F = Fmt<ST>;
-  if constexpr (VEC == 1) {
-    F::store_elem(p, idx, x[0]);
-  } else if constexpr (ST == COSM_STORE_FP32) {
-    float *q = static_cast<float *>(p) + idx;
-    if constexpr (VEC == 4) {
-      *(gvec<hbm_f32x4>)(q) = hbm_f32x4{x[0], x[1], x[2], x[3]};
-    } else {
-      *(gvec<hbm_f32x2>)(q) = hbm_f32x2{x[0], x[1]};
-    }
-  } else if constexpr (ST == COSM_STORE_FIX32) {
-    uint32_t *q = static_cast<uint32_t *>(p) + idx;
-    if constexpr (VEC == 4) {
-      *(gvec<hbm_u32x4>)(q) = hbm_u32x4{F::enc(x[0]), F::enc(x[1]), F::enc(x[2]), F::enc(x[3])};
-    } else {
-      *(gvec<hbm_u32x2>)(q) = hbm_u32x2{F::enc(x[0]), F::enc(x[1])};
-    }
-  } else {
-    uint16_t *q = static_cast<uint16_t *>(p) + idx;
-    if constexpr (VEC == 4) {
-      *(gvec<hbm_u32x2>)(q) = hbm_u32x2{F::enc(x[0]) | (F::enc(x[1]) << 16),
-                                        F::enc(x[2]) | (F::enc(x[3]) << 16)};
-    } else {
-      *(gvec<uint32_t>)(q) = F::enc(x[0]) | (F::enc(x[1]) << 16);
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Device-memory forms: one launch per colour class.  HBM form: a wave covers
 // 64 VEC consecutive replicas of one edge (coalesced rows of the [n][R]
 // layout, VEC per lane).  PLAIN form: one replica, a thread per edge.
@@ -545,23 +497,6 @@ int launch_check(const char *what) {
   return COSM_OK;
 }
 
-// Step size of sweep t (1-based) in turns, exactly as the device evaluates it.
-float host_alpha(const Schedule &sc, int64_t t) {
-  if (sc.grid) {
-    const int64_t q = (sc.a0_units * (sc.S - t + 1) + sc.S / 2) / sc.S;
-    return (float)q * sc.aunit;
-  }
-  return (float)(sc.S - t + 1) * (sc.alpha0_turns / (float)sc.S);
-}
-
-float host_twist(const Schedule &sc, int64_t t) {
-  if (sc.grid) {
-    const int64_t q = (sc.a0_units * (sc.S - t + 1) + sc.S / 2) / sc.S;
-    return (float)(sc.twist_num2 * q) * sc.tunit;
-  }
-  return sc.dwt_ratio * host_alpha(sc, t);
-}
-
 template <int ST, int W, int EMAX, bool EXACT, bool FUSE, bool LAZY, bool RD = false>
 int launch_lds_k(cosm_state *s, const LdsArgs &a) {
   const size_t lds = s->shape.lds_bytes;
@@ -644,14 +579,6 @@ int sweeps_lds_st(cosm_state *s, int64_t n_sweeps) {
   if (W == 2) return launch_lds_w<ST, 2>(s, a);
   if (W == 1) return launch_lds_w<ST, 1>(s, a);
   return set_error(COSM_EINVAL, "unsupported replicas per workgroup");
-}
-
-// Replicas per lane of the HBM kernels: the widest of 4, 2, 1 that keeps every
-// access aligned (R, the first replica and the count all multiples of it).
-int hbm_vec(int32_t R, int32_t rbeg, int32_t rcount) {
-  for (int v : {4, 2})
-    if (R % v == 0 && rbeg % v == 0 && rcount % v == 0) return v;
-  return 1;
 }
 
 template <int ST, int VEC>
@@ -825,7 +752,9 @@ template <int ST> struct SweepFn {
         if (s->lds.stream) return launch_sweeps_stream(s, n);
         if (s->lds.rstream) return launch_sweeps_rstream(s, n);
         return sweeps_lds_st<ST>(s, n);
-      case COSM_RES_HBM: return sweeps_hbm_st<ST>(s, n);
+      case COSM_RES_HBM:
+        if (!s->dual_count.empty()) return launch_sweeps_dual_hbm(s, n);
+        return sweeps_hbm_st<ST>(s, n);
       case COSM_RES_PLAIN: return sweeps_plain_st<ST>(s, n);
     }
     return set_error(COSM_EINVAL, "unknown residency");
@@ -923,6 +852,25 @@ int lds_capacity_bytes() {
   if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
     return 65536;
   return v;
+}
+
+namespace {
+template <int ST> struct FieldHbmFn {
+  static int run(cosm_state *s, float alpha, int32_t rbeg, int32_t rcount) {
+    return field_hbm_st<ST>(s, alpha, rbeg, rcount);
+  }
+};
+template <int ST> struct DwtHbmFn {
+  static int run(cosm_state *s, int64_t t, int32_t rbeg, int32_t rcount) {
+    return dwt_hbm_st<ST>(s, t, rbeg, rcount);
+  }
+};
+}  // namespace
+int launch_field_hbm(cosm_state *s, float alpha, int32_t rbeg, int32_t rcount) {
+  return dispatch_storage<FieldHbmFn>(s->p.storage, s, alpha, rbeg, rcount);
+}
+int launch_dwt_hbm(cosm_state *s, int64_t t, int32_t rbeg, int32_t rcount) {
+  return dispatch_storage<DwtHbmFn>(s->p.storage, s, t, rbeg, rcount);
 }
 
 int launch_init(cosm_state *s) { return dispatch_storage<InitFn>(s->p.storage, s); }

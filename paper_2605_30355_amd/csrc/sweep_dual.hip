@@ -264,88 +264,102 @@ bool dual_form_default(const cosm_state &s, int32_t W, int32_t blocks, int32_t c
   return blocks <= cus && s.p.lds_form <= COSM_LDS_FORM_PAIR && dual_form_supported(s, W);
 }
 
-// The entries of every round (host).  Round q holds classes 2q and 2q + 1 (an
-// odd last class alone: J = 0 for the second).  Rows are the vertices in order;
-// entries in order of their first vertex, so that on lattices neighbouring
-// lanes read neighbouring rows.
+// The entries of every round.  Round q holds classes 2q and 2q + 1 (an odd last
+// class alone), entries in order of their first vertex, so that on lattices
+// neighbouring lanes or waves read neighbouring rows.
+std::vector<std::vector<DualEntry>> dual_entries(const cosm_state &s) {
+  const int32_t n = s.n, C = s.C, rounds = (C + 1) / 2;
+  // edge of each vertex in a class
+  std::vector<int32_t> e0((size_t)n), e1((size_t)n);
+  std::vector<std::vector<int32_t>> by_class((size_t)C);
+  for (int64_t k = 0; k < s.m; k++)
+    by_class[(size_t)s.h_colour[(size_t)k]].push_back((int32_t)k);
+  auto edges_of = [&](int32_t c, std::vector<int32_t> &at) {
+    std::fill(at.begin(), at.end(), -1);
+    if (c >= C) return;
+    for (int32_t k : by_class[(size_t)c]) {
+      at[(size_t)s.h_eu[(size_t)k]] = k;
+      at[(size_t)s.h_ev[(size_t)k]] = k;
+    }
+  };
+  std::vector<std::vector<DualEntry>> out((size_t)rounds);
+  for (auto &l : out) l.reserve((size_t)n / 2 + 1);
+  std::vector<uint8_t> done((size_t)n);
+  for (int32_t q = 0; q < rounds; q++) {
+    edges_of(2 * q, e0);
+    edges_of(2 * q + 1, e1);
+    std::fill(done.begin(), done.end(), 0);
+    // an endpoint's edge in class 2q: the partner, J and whether it is the v there
+    auto end = [&](int32_t x, int32_t *partner, int32_t *J, int32_t *flip) {
+      const int32_t k = x >= 0 ? e0[(size_t)x] : -1;
+      *partner = -1;
+      *J = 0;
+      *flip = 0;
+      if (k < 0) return;
+      *flip = s.h_ev[(size_t)k] == x ? 1 : 0;
+      *partner = *flip ? s.h_eu[(size_t)k] : s.h_ev[(size_t)k];
+      *J = s.h_J[(size_t)k];
+    };
+    auto push = [&](int32_t u, int32_t v, int32_t J) {
+      DualEntry e{};
+      e.u = u;
+      e.v = v;
+      e.J = J;
+      end(u, &e.pu, &e.Ju, &e.fu);
+      end(v, &e.pv, &e.Jv, &e.fv);
+      out[(size_t)q].push_back(e);
+    };
+    int32_t lone = -1;  // a vertex without an edge in class 2q + 1, waiting for another
+    for (int32_t x = 0; x < n; x++) {
+      if (done[(size_t)x]) continue;
+      const int32_t k = e1[(size_t)x];
+      if (k >= 0) {
+        const int32_t u = s.h_eu[(size_t)k], v = s.h_ev[(size_t)k];
+        done[(size_t)u] = done[(size_t)v] = 1;
+        push(u, v, s.h_J[(size_t)k]);
+      } else if (lone < 0) {
+        lone = x;
+      } else {
+        push(lone, x, 0);
+        lone = -1;
+      }
+    }
+    if (lone >= 0) push(lone, -1, 0);
+  }
+  return out;
+}
+
 int dual_schedule_for(const cosm_state &s, int32_t W, LdsSchedule *out) {
   if (!dual_form_supported(s, W))
     return set_error(COSM_ERANGE, "the two-class form does not apply");
-  const int32_t n = s.n, C = s.C, rounds = (C + 1) / 2;
-  const int64_t m = s.m;
+  const int32_t n = s.n, rounds = (s.C + 1) / 2;
   LdsSchedule L;
   L.G = W == 1 ? 32 : 64 / W;
   L.n_rows = n;
   L.slot_vertex.resize((size_t)n);
   for (int32_t v = 0; v < n; v++) L.slot_vertex[(size_t)v] = v;
-  // edge of each vertex in each class
-  std::vector<int32_t> edge_at((size_t)C * n, -1);
-  for (int64_t k = 0; k < m; k++) {
-    const size_t c = (size_t)s.h_colour[(size_t)k];
-    edge_at[c * n + s.h_eu[(size_t)k]] = (int32_t)k;
-    edge_at[c * n + s.h_ev[(size_t)k]] = (int32_t)k;
-  }
-  struct Entry {
-    int32_t u, v, e;  // e: the edge of class 2q + 1, or -1
-  };
-  std::vector<std::vector<Entry>> lists((size_t)rounds);
+  const std::vector<std::vector<DualEntry>> lists = dual_entries(s);
   size_t most = 0;
-  for (int32_t q = 0; q < rounds; q++) {
-    const int32_t c1 = 2 * q + 1;
-    std::vector<uint8_t> done((size_t)n, 0);
-    int32_t lone = -1;  // a vertex without an edge in class c1, waiting for another
-    auto &L1 = lists[(size_t)q];
-    for (int32_t x = 0; x < n; x++) {
-      if (done[(size_t)x]) continue;
-      const int32_t e = c1 < C ? edge_at[(size_t)c1 * n + x] : -1;
-      if (e >= 0) {
-        const int32_t u = s.h_eu[(size_t)e], v = s.h_ev[(size_t)e];
-        done[(size_t)u] = done[(size_t)v] = 1;
-        L1.push_back({u, v, e});
-      } else if (lone < 0) {
-        lone = x;
-      } else {
-        L1.push_back({lone, x, -1});
-        lone = -1;
-      }
-    }
-    if (lone >= 0) L1.push_back({lone, -1, -1});
-    most = std::max(most, L1.size());
-  }
+  for (const auto &l : lists) most = std::max(most, l.size());
   L.nth = (int32_t)std::max<size_t>(64, (most + 63) / 64 * 64);
   const int32_t nth = L.nth;
   L.dual_words.assign((size_t)rounds * kDualWords * nth, 0u);
-  for (int32_t q = 0; q < rounds; q++) {
-    const int32_t c0 = 2 * q;
+  for (int32_t q = 0; q < rounds; q++)
     for (int32_t t = 0; t < nth; t++) {
-      const bool real = (size_t)t < lists[(size_t)q].size();
-      const Entry e = real ? lists[(size_t)q][(size_t)t] : Entry{-1, -1, -1};
-      const uint32_t du = (uint32_t)(n + (t & 31)), dv = du + 32u;  // dummy rows
-      // the class c0 edge of an endpoint: its partner's row, J and the flip
-      auto end = [&](int32_t x, uint32_t dummy, uint32_t *row, float *J, uint32_t *flip) {
-        const int32_t k = x >= 0 ? edge_at[(size_t)c0 * n + x] : -1;
-        *row = dummy;
-        *J = 0.0f;
-        *flip = 0;
-        if (k < 0) return;
-        *flip = s.h_ev[(size_t)k] == x ? 1u : 0u;
-        *row = (uint32_t)(*flip ? s.h_eu[(size_t)k] : s.h_ev[(size_t)k]);
-        *J = (float)s.h_J[(size_t)k];
-      };
-      uint32_t ru, rv, fu, fv;
-      float Ju, Jv;
-      end(e.u, du, &ru, &Ju, &fu);
-      end(e.v, dv, &rv, &Jv, &fv);
-      const float Jp = e.e >= 0 ? (float)s.h_J[(size_t)e.e] : 0.0f;
-      const uint32_t u = e.u >= 0 ? (uint32_t)e.u : du, v = e.v >= 0 ? (uint32_t)e.v : dv;
-      const uint32_t w[kDualWords] = {u | v << 16, ru | rv << 16,
-                                      __builtin_bit_cast(uint32_t, Jp),
-                                      __builtin_bit_cast(uint32_t, Ju),
-                                      __builtin_bit_cast(uint32_t, Jv), fu | fv << 1};
+      const auto &l = lists[(size_t)q];
+      DualEntry e{-1, -1, -1, -1, 0, 0, 0, 0, 0};
+      if ((size_t)t < l.size()) e = l[(size_t)t];
+      // (lanes and endpoints without an edge take dummy rows)
+      const uint32_t du = (uint32_t)(n + (t & 31)), dv = du + 32u;
+      auto row = [](int32_t x, uint32_t dummy) { return x >= 0 ? (uint32_t)x : dummy; };
+      auto word = [](int32_t J) { return __builtin_bit_cast(uint32_t, (float)J); };
+      const uint32_t w[kDualWords] = {row(e.u, du) | row(e.v, dv) << 16,
+                                      row(e.pu, du) | row(e.pv, dv) << 16,
+                                      word(e.J), word(e.Ju), word(e.Jv),
+                                      (uint32_t)(e.fu | e.fv << 1)};
       for (int k = 0; k < kDualWords; k++)
         L.dual_words[((size_t)q * kDualWords + k) * nth + t] = w[k];
     }
-  }
   L.dual = true;
   L.fuse = true;
   *out = std::move(L);
