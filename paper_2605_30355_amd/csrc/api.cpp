@@ -461,7 +461,10 @@ int init_state(cosm_state **out, int32_t n, int64_t m, const int32_t *eu, const 
   s->h_ev.assign(ev, ev + m);
   s->h_J.assign(J, J + m);
   s->sumJ = 0;
-  for (int64_t k = 0; k < m; k++) s->sumJ += J[k];
+  for (int64_t k = 0; k < m; k++) {
+    s->sumJ += J[k];
+    s->sum_abs_J += std::llabs((int64_t)J[k]);
+  }
   {
     std::vector<int64_t> wdeg((size_t)n, 0);
     for (int64_t k = 0; k < m; k++) {
@@ -496,6 +499,7 @@ int init_state(cosm_state **out, int32_t n, int64_t m, const int32_t *eu, const 
     }
   }
   s->n_slots = n;
+  s->cus = device_cu_count();
 
   // incidence lists (full-gradient form)
   std::vector<int32_t> inc_off;

@@ -1003,6 +1003,7 @@ struct ReadoutArgs {
   int32_t *best_p;
   int32_t n, R, B, grid;
   int64_t m;
+  int64_t sumJ;           // sum of J
 };
 
 // Readout, Algorithm 1 binarization, of replica r by one workgroup.  Bisector p

@@ -265,11 +265,13 @@ struct cosm_state {
   cosm::Schedule sched{};
   int32_t n_slots = 0;
   int32_t max_class = 0;
+  int32_t cus = 256;  // compute units of the device
   mutable std::vector<uint8_t> indep;  // independent set of the register forms, once found
   cosm::LdsSchedule lds;  // resolved lane schedule of the LDS form
   std::vector<int32_t> lds_widths;  // row widths (words) that fit, for the autotuner
   bool has_h = false;
   int64_t sumJ = 0;                 // sum of J over the edges
+  int64_t sum_abs_J = 0;            // sum of |J|
   int64_t wdeg_max = 0;             // largest sum of |J| (and |h|) at one vertex
   size_t opt_temp_bytes = 0;        // segmented sort workspace (optimal readout)
   std::vector<int32_t> h_eu, h_ev, h_J, h_h, h_colour;
@@ -461,6 +463,12 @@ inline size_t lds_sweep_bytes(int32_t n_rows, int W, int32_t C) {
 }
 
 size_t readout_lds_bytes(int32_t n, int32_t B);
+// Replicas per workgroup of the grouped readout (readout_group.hpp; 0: not in it):
+// at most 127 bisectors, no bias fields, the most of 4, 2, 1 whose codes fit the LDS
+// and that still give every CU a workgroup.
+int readout_group_size(int32_t n, int32_t B, int32_t R, int32_t cus);
+constexpr int32_t kReadoutGroupBisectors = 127;
+constexpr int64_t kReadoutSmallSum = (int64_t)1 << 30;
 // The readout keeps its per-vertex codes in LDS up to this many bytes.
 constexpr size_t kReadoutLdsLimit = 163840;
 }  // namespace cosm

@@ -26,6 +26,7 @@
 #include "hbm_vec.hpp"
 #include "internal.hpp"
 #include "lds_args.hpp"
+#include "readout_group.hpp"
 
 namespace cosm {
 
@@ -451,6 +452,12 @@ __global__ void __launch_bounds__(256) k_readout(const ReadoutArgs a) {
   readout_block<ST>(a, xcd_block(blockIdx.x, gridDim.x), sm64);
 }
 
+template <int ST, int Q, bool SMALL>
+__global__ void __launch_bounds__(1024) k_readout_group(const ReadoutArgs a) {
+  extern __shared__ int64_t sm64[];
+  readout_group<ST, Q, SMALL>(a, xcd_block(blockIdx.x, gridDim.x) * Q, sm64);
+}
+
 // Energy (Eq. (1)) and cut (Eq. (14), w = -J) of caller-supplied spins [R][n].
 __global__ void __launch_bounds__(256) k_energy(const int8_t *spins, const int32_t *eu,
                                                 const int32_t *ev, const int32_t *J,
@@ -679,6 +686,23 @@ int sweeps_plain_st(cosm_state *s, int64_t n_sweeps) {
   return COSM_OK;
 }
 
+template <int ST, int Q, bool SMALL>
+int readout_group_k(cosm_state *s, const ReadoutArgs &a) {
+  const size_t lds = readout_group_lds(a.n, a.B, Q);
+  (void)hipFuncSetAttribute((const void *)k_readout_group<ST, Q, SMALL>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  const int threads = a.n >= 8192 ? 1024 : a.n >= 2048 ? 512 : 256;
+  hipLaunchKernelGGL((k_readout_group<ST, Q, SMALL>), dim3((unsigned)((a.R + Q - 1) / Q)),
+                     dim3(threads), lds, s->stream, a);
+  return launch_check("k_readout_group");
+}
+
+template <int ST, int Q>
+int readout_group_q(cosm_state *s, const ReadoutArgs &a) {
+  return s->sum_abs_J < kReadoutSmallSum ? readout_group_k<ST, Q, true>(s, a)
+                                         : readout_group_k<ST, Q, false>(s, a);
+}
+
 template <int ST>
 int readout_st(cosm_state *s) {
   ReadoutArgs a{};
@@ -697,6 +721,14 @@ int readout_st(cosm_state *s) {
   a.grid = s->sched.grid;
   a.m = s->m;
   a.code_global = s->d.codes;
+  a.sumJ = s->sumJ;
+  if (!s->has_h) {
+    switch (readout_group_size(s->n, a.B, s->R, s->cus)) {
+      case 4: return readout_group_q<ST, 4>(s, a);
+      case 2: return readout_group_q<ST, 2>(s, a);
+      case 1: return readout_group_q<ST, 1>(s, a);
+    }
+  }
   const size_t lds = readout_lds_bytes(a.code_global != nullptr ? 0 : s->n, a.B);
   (void)hipFuncSetAttribute((const void *)k_readout<ST>, hipFuncAttributeMaxDynamicSharedMemorySize,
                       (int)lds);
@@ -840,6 +872,13 @@ bool lazy16(const cosm_state &s) {
   return (st == COSM_STORE_FP16 || st == COSM_STORE_BF16 || st == COSM_STORE_FP16_PK) &&
          s.p.update == COSM_UPDATE_SCS &&
          s.sched.dwt_period > 0 && wrap_drift_turns(s) < 0.5;
+}
+
+int readout_group_size(int32_t n, int32_t B, int32_t R, int32_t cus) {
+  if (B > kReadoutGroupBisectors) return 0;
+  int Q = 4;
+  while (Q > 1 && (readout_group_lds(n, B, Q) > kReadoutLdsLimit || (R + Q - 1) / Q < cus)) Q /= 2;
+  return readout_group_lds(n, B, Q) <= kReadoutLdsLimit ? Q : 0;
 }
 
 size_t readout_lds_bytes(int32_t n, int32_t B) {
