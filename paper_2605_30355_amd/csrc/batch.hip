@@ -22,6 +22,7 @@
 
 #include "device_common.hpp"
 #include "internal.hpp"
+#include "readout_group.hpp"
 
 namespace cosm {
 namespace {
@@ -30,6 +31,7 @@ constexpr int kBatchThreads = 1024;
 // Dynamic LDS of the persistent kernel: rows, reference angles and slot counts,
 // then 256 bytes of control words at the end.
 constexpr int kLdsBudget = 163840;
+constexpr int kReadoutQ = 4;          // replicas per workgroup of the grouped readout
 constexpr int kMaxSetReplicas = 256;  // replica sets x replicas per set, per item
 
 // One graph as the batch kernels see it.
@@ -45,6 +47,7 @@ struct GraphDev {
   ReadoutArgs ro;
   int32_t grid;
   int32_t lazy;               // 16-bit float phases wrapped at the twists only
+  int32_t small_sum;          // the sum of |J| is below kReadoutSmallSum
   uint32_t ishift;            // initial phases: (draw >> ishift) * iscale
   float iscale;
 };
@@ -58,7 +61,7 @@ struct RunDesc {
   int32_t n_items;
   int32_t n_run;              // graphs in this run
   int64_t total_phases;       // sum of n * R over the run's graphs
-  int32_t total_replicas;     // sum of R
+  int32_t total_units;        // sum of ceil(R / replicas per readout workgroup)
   int32_t counter;            // work-item counter of k_batch_sweeps
 };
 
@@ -67,7 +70,7 @@ __global__ void k_batch_reset(RunDesc *rd) {
 }
 
 // run_graphs[k]: graph index of the k-th graph of the run; phase_prefix and
-// rep_prefix: exclusive prefix sums over the run (length n_run + 1).
+// unit_prefix: exclusive prefix sums over the run (length n_run + 1).
 template <int ST>
 __global__ void __launch_bounds__(256) k_batch_init(const GraphDev *graphs, const RunDesc *rd,
                                                     const int32_t *run_graphs,
@@ -244,20 +247,52 @@ __global__ void __launch_bounds__(kBatchThreads) k_batch_sweeps(const GraphDev *
   }
 }
 
+// The graph of readout unit `unit` of a run, and which unit of the graph it is.
+__device__ __forceinline__ const GraphDev &unit_graph(const GraphDev *graphs,
+                                                      const int32_t *run_graphs,
+                                                      const int32_t *unit_prefix, int32_t n_run,
+                                                      int32_t unit, int32_t *local) {
+  int32_t lo = 0, hi = n_run - 1;
+  while (lo < hi) {
+    const int32_t mid = (lo + hi + 1) >> 1;
+    if (unit_prefix[mid] <= unit) lo = mid; else hi = mid - 1;
+  }
+  *local = unit - unit_prefix[lo];
+  return graphs[run_graphs[lo]];
+}
+
+// Batches past the grouped readout's limits (more than 127 bisectors, or a max_n past
+// its codes): one replica per workgroup.
 template <int ST>
 __global__ void __launch_bounds__(256) k_batch_readout(const GraphDev *graphs, const RunDesc *rd,
                                                        const int32_t *run_graphs,
-                                                       const int32_t *rep_prefix) {
+                                                       const int32_t *unit_prefix) {
   extern __shared__ int64_t sm64[];
-  const int32_t total = rd->total_replicas, nr = rd->n_run;
+  const int32_t total = rd->total_units, nr = rd->n_run;
   for (int32_t b = blockIdx.x; b < total; b += gridDim.x) {
-    int32_t lo = 0, hi = nr - 1;
-    while (lo < hi) {
-      const int32_t mid = (lo + hi + 1) >> 1;
-      if (rep_prefix[mid] <= b) lo = mid; else hi = mid - 1;
-    }
-    const GraphDev &g = graphs[run_graphs[lo]];
-    readout_block<ST>(g.ro, b - rep_prefix[lo], sm64);
+    int32_t r;
+    const GraphDev &g = unit_graph(graphs, run_graphs, unit_prefix, nr, b, &r);
+    readout_block<ST>(g.ro, r, sm64);
+    __syncthreads();
+  }
+}
+
+// kReadoutQ replicas per workgroup (readout_group.hpp); the units of a graph that read
+// the same lines of its phases run on one XCD (gridDim.x is a multiple of its 8).  24
+// graphs of 778 - 18769 vertices x 256 replicas, FP32: 1236 -> 338 us.
+template <int ST>
+__global__ void __launch_bounds__(1024) k_batch_readout_group(const GraphDev *graphs,
+                                                              const RunDesc *rd,
+                                                              const int32_t *run_graphs,
+                                                              const int32_t *unit_prefix) {
+  extern __shared__ int64_t sm64[];
+  const int32_t total = rd->total_units, nr = rd->n_run;
+  for (int32_t b = blockIdx.x; b < total; b += gridDim.x) {
+    int32_t q;
+    const GraphDev &g =
+        unit_graph(graphs, run_graphs, unit_prefix, nr, xcd_block(b, total), &q);
+    if (g.small_sum) readout_group<ST, kReadoutQ, true>(g.ro, q * kReadoutQ, sm64);
+    else readout_group<ST, kReadoutQ, false>(g.ro, q * kReadoutQ, sm64);
     __syncthreads();
   }
 }
@@ -290,12 +325,13 @@ struct cosm_batch {
   int32_t max_graphs = 0, max_n = 0, max_items = 0, max_bisectors = 0;
   bool own_stream = false;
   size_t lds_budget = 0, readout_lds = 0;
+  bool grouped = false;     // the grouped readout applies
   int32_t cus = 256;
   std::vector<BatchGraphHost *> graphs;
   GraphDev *d_graphs = nullptr;
   Item *d_items = nullptr;
   RunDesc *d_run = nullptr;
-  int32_t *d_run_graphs = nullptr, *d_rep_prefix = nullptr;
+  int32_t *d_run_graphs = nullptr, *d_unit_prefix = nullptr;
   int64_t *d_phase_prefix = nullptr;
   // the captured run, one per sweep variant (1: every graph FP32 on the grid)
   hipGraph_t graph[2] = {nullptr, nullptr};
@@ -323,8 +359,14 @@ void enqueue_run(cosm_batch *b) {
     hipLaunchKernelGGL((k_batch_sweeps<ST, false>), dim3(b->cus), dim3(kBatchThreads),
                        (size_t)kLdsBudget, b->stream, b->d_graphs, b->d_items, b->d_run);
   }
-  hipLaunchKernelGGL((k_batch_readout<ST>), dim3(4096), dim3(256), b->readout_lds, b->stream,
-                     b->d_graphs, b->d_run, b->d_run_graphs, b->d_rep_prefix);
+  if (b->grouped)
+    hipLaunchKernelGGL((k_batch_readout_group<ST>), dim3(2048),
+                       dim3(b->max_n >= 8192 ? 1024 : b->max_n >= 2048 ? 512 : 256),
+                       b->readout_lds, b->stream, b->d_graphs, b->d_run, b->d_run_graphs,
+                       b->d_unit_prefix);
+  else
+    hipLaunchKernelGGL((k_batch_readout<ST>), dim3(4096), dim3(256), b->readout_lds, b->stream,
+                       b->d_graphs, b->d_run, b->d_run_graphs, b->d_unit_prefix);
 }
 
 template <int ST>
@@ -334,7 +376,8 @@ void set_attrs(cosm_batch *b) {
   if constexpr (ST == COSM_STORE_FP32)
     (void)hipFuncSetAttribute((const void *)k_batch_sweeps<ST, true>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget);
-  (void)hipFuncSetAttribute((const void *)k_batch_readout<ST>,
+  (void)hipFuncSetAttribute(b->grouped ? (const void *)k_batch_readout_group<ST>
+                                       : (const void *)k_batch_readout<ST>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->readout_lds);
 }
 
@@ -407,14 +450,15 @@ int prepare_run(cosm_batch *b, const std::vector<int32_t> &ids, bool fill = true
   rd.n_items = (int32_t)sorted.size();
   rd.n_run = count;
   std::vector<int64_t> phase_prefix((size_t)count + 1, 0);
-  std::vector<int32_t> rep_prefix((size_t)count + 1, 0);
+  std::vector<int32_t> unit_prefix((size_t)count + 1, 0);
   for (int32_t k = 0; k < count; k++) {
     const GraphDev &d = b->graphs[(size_t)ids[(size_t)k]]->dev;
     phase_prefix[(size_t)k + 1] = phase_prefix[(size_t)k] + (int64_t)d.n * d.R;
-    rep_prefix[(size_t)k + 1] = rep_prefix[(size_t)k] + d.R;
+    const int32_t q = b->grouped ? kReadoutQ : 1;
+    unit_prefix[(size_t)k + 1] = unit_prefix[(size_t)k] + (d.R + q - 1) / q;
   }
   rd.total_phases = phase_prefix[(size_t)count];
-  rd.total_replicas = rep_prefix[(size_t)count];
+  rd.total_units = unit_prefix[(size_t)count];
   std::vector<GraphDev> gd;
   for (BatchGraphHost *g : b->graphs) gd.push_back(g->dev);
   int rc = COSM_OK;
@@ -427,7 +471,7 @@ int prepare_run(cosm_batch *b, const std::vector<int32_t> &ids, bool fill = true
   up(b->d_items, sorted.data(), sorted.size() * sizeof(Item));
   up(b->d_run, &rd, sizeof rd);
   up(b->d_run_graphs, ids.data(), ids.size() * 4);
-  up(b->d_rep_prefix, rep_prefix.data(), rep_prefix.size() * 4);
+  up(b->d_unit_prefix, unit_prefix.data(), unit_prefix.size() * 4);
   up(b->d_phase_prefix, phase_prefix.data(), phase_prefix.size() * 8);
   if (rc) return rc;
   // the host tables above are read by the copies: wait before they go out of scope
@@ -574,6 +618,11 @@ int cosm_batch_create(cosm_batch **out, int32_t storage, int32_t max_graphs, int
     delete b;
     return set_error(COSM_ERANGE, "max_n too large for the readout");
   }
+  const size_t grouped_lds = readout_group_lds(max_n, max_bisectors, kReadoutQ);
+  if (max_bisectors <= kReadoutGroupBisectors && grouped_lds <= kReadoutLdsLimit) {
+    b->grouped = true;
+    b->readout_lds = grouped_lds;
+  }
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) == hipSuccess &&
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
@@ -587,7 +636,7 @@ int cosm_batch_create(cosm_batch **out, int32_t storage, int32_t max_graphs, int
   alloc((void **)&b->d_items, sizeof(Item) * b->max_items);
   alloc((void **)&b->d_run, sizeof(RunDesc));
   alloc((void **)&b->d_run_graphs, sizeof(int32_t) * max_graphs);
-  alloc((void **)&b->d_rep_prefix, sizeof(int32_t) * (max_graphs + 1));
+  alloc((void **)&b->d_unit_prefix, sizeof(int32_t) * (max_graphs + 1));
   alloc((void **)&b->d_phase_prefix, sizeof(int64_t) * (max_graphs + 1));
   if (rc == COSM_OK && (hipEventCreate(&b->e0) != hipSuccess || hipEventCreate(&b->e1) != hipSuccess))
     rc = set_error(COSM_EDEVICE, "hipEventCreate");
@@ -623,7 +672,7 @@ int cosm_batch_destroy(cosm_batch *b) {
   (void)hipFree(b->d_items);
   (void)hipFree(b->d_run);
   (void)hipFree(b->d_run_graphs);
-  (void)hipFree(b->d_rep_prefix);
+  (void)hipFree(b->d_unit_prefix);
   (void)hipFree(b->d_phase_prefix);
   if (b->e0) (void)hipEventDestroy(b->e0);
   if (b->e1) (void)hipEventDestroy(b->e1);
@@ -767,6 +816,12 @@ int cosm_batch_add_graph(cosm_batch *b, int32_t n, int64_t m, const int32_t *eu,
   ro.B = s.p.n_bisectors;
   ro.grid = sc.grid;
   ro.m = m;
+  int64_t sum_abs_J = 0;
+  for (int32_t j : s.h_J) {
+    ro.sumJ += j;
+    sum_abs_J += std::abs((int64_t)j);
+  }
+  d.small_sum = sum_abs_J < kReadoutSmallSum;
   // the lane schedule of candidate k: its descriptors, slot counts and slot
   // map on the device, its width and replica sets in the descriptor
   auto install = [&](size_t k) {
