@@ -40,6 +40,9 @@ struct GraphDev {
   const EdgeDesc *desc;       // lane schedule for kBatchThreads threads
   const int32_t *Kc;          // [C]
   const int32_t *slot_vertex; // [n]
+  const uint32_t *words;      // the lane schedule as words, or null (batch_words)
+  const int32_t *Kw;          // [C]
+  float jscale;               // |J| of every edge (words)
   int32_t n, R, C, total_slots, W;
   int64_t S;                  // sweeps per trial
   SweepSchedule sch;          // at t0 = 0
@@ -94,18 +97,134 @@ __global__ void __launch_bounds__(256) k_batch_init(const GraphDev *graphs, cons
   }
 }
 
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t word_buffer(const uint32_t *words, int total) {
+  const uint64_t at = (uint64_t)words;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)at);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(at >> 32));
+  const int bytes = __builtin_amdgcn_readfirstlane((total + kStreamRepeat) * kBatchThreads * 8);
+  return __builtin_amdgcn_make_buffer_rsrc((void *)((uint64_t)hi << 32 | lo), (short)0, bytes,
+                                           0x00020000);
+}
+
+// One sweep's classes for an item of one replica set with the schedule as words (byte
+// offsets and signs; empty slots hold dummy rows, so that no lane branches).  The rows
+// of slot k + 1 are read before slot k is computed and written (within a class they
+// are disjoint): the LDS latency of one slot overlaps the arithmetic of the other, as
+// several sets overlap in edge_rows_sets.  A holds slot j's words and B slot j + 1's,
+// read with buffer loads whose slot offset is a scalar and refilled as soon as their
+// rows are read.  Kw[c] (in LDS): slots of class c, and in the high half the lanes of
+// the last one; waves past them skip it.
+// 24 graphs of 778 - 18769 vertices x 256 replicas x 500 sweeps, whole passes before and
+// after the words (FP32: and the wrap at the twists): FP32 40.6 -> 37.3 ms (k_batch_sweeps
+// 32.1 -> 26.9), FP16 49.0 -> 40.0, BF16 44.4 -> 38.9, FIX16 34.4 -> 30.1, FIX32 47.6 ->
+// 41.9, FP16_PK 41.0 -> 36.1.  The vector unit is 54 % busy and the LDS 44 % then, one
+// workgroup per CU; words two loads ahead and in pairs of slots measured 29.2 ms.
+template <int W, typename UpdateFn>
+__device__ __forceinline__ void word_classes(const uint32_t *words_any, const int32_t *Kw,
+                                             int C, int total, su2 &A, su2 &B, uint32_t &j,
+                                             float amag, UpdateFn update) {
+  const uint32_t lane8 = threadIdx.x * 8u;
+  constexpr uint32_t stride8 = kBatchThreads * 8u;
+  // (a buffer descriptor that the compiler takes for divergent would cost every load a
+  // loop over its values)
+  const __amdgpu_buffer_rsrc_t words = word_buffer(words_any, total);
+  const int32_t wave_base = __builtin_amdgcn_readfirstlane((int)threadIdx.x & ~63);
+  auto at = [&](uint32_t slot) -> su2 {
+    return __builtin_amdgcn_raw_buffer_load_b64(
+        words, lane8, __builtin_amdgcn_readfirstlane(slot * stride8), 0);
+  };
+  // slot's words into d, whose old ones x was made from: the empty statement keeps the
+  // load behind all uses of the old words, so that it can take their registers (in
+  // others, a copy at the loop's head would wait for it at once)
+  auto refill = [&](su2 &d, auto &x, uint32_t slot) {
+    uint32_t off = __builtin_amdgcn_readfirstlane(slot * stride8);
+    asm volatile("" : "+v"(x.au), "+v"(x.av), "+v"(x.aJ), "+s"(off));
+    d = __builtin_amdgcn_raw_buffer_load_b64(words, lane8, off, 0);
+  };
+  struct Flight {
+    uint32_t u[W], v[W], au, av;
+    float aJ;
+  } f[2];
+  auto read = [&](Flight &x, const su2 &d) {
+    x.au = d.x & 0x7fffffffu;
+    x.av = d.y & 0x7fffffffu;  // (a new value too: the refill may take the words' registers)
+    // (the sign bit from the word, the rest from amag: one v_bitop3)
+    x.aJ = __uint_as_float(
+        __builtin_amdgcn_bitop3_b32(d.x, __float_as_uint(amag), 0x80000000u, 0xe4));
+  };
+  auto rows = [&](Flight &x) {
+    row_load<W>(x.au, x.u);
+    row_load<W>(x.av, x.v);
+  };
+  auto finish = [&](Flight &x) {
+    update(x.u, x.v, x.aJ);
+    row_store<W>(x.au, x.u);
+    row_store<W>(x.av, x.v);
+  };
+  for (int c = 0; c < C; c++) {
+    const uint32_t kw = (uint32_t)__builtin_amdgcn_readfirstlane(Kw[c]);
+    const int kc = (int)(kw & 0xffffu);
+    if (kc == 0) continue;
+    const int mine = wave_base < (int)(kw >> 16) ? kc : kc - 1;
+    int k = 0;
+    if (mine >= 2) {
+      read(f[0], A);
+      refill(A, f[0], j + 2);
+      rows(f[0]);
+      read(f[1], B);
+      refill(B, f[1], j + 3);
+      rows(f[1]);
+      finish(f[0]);
+      for (k = 2; k + 2 <= mine; k += 2) {
+        read(f[0], A);
+        refill(A, f[0], j + k + 2);
+        rows(f[0]);
+        finish(f[1]);
+        read(f[1], B);
+        refill(B, f[1], j + k + 3);
+        rows(f[1]);
+        finish(f[0]);
+      }
+      if (k < mine) {
+        read(f[0], A);
+        rows(f[0]);
+        finish(f[1]);
+        finish(f[0]);
+        A = B;
+        B = at(j + k + 2);
+      } else {
+        finish(f[1]);
+      }
+    } else if (mine == 1) {
+      read(f[0], A);
+      rows(f[0]);
+      finish(f[0]);
+      A = B;
+      B = at(j + 2);
+    }
+    if (mine < kc) {  // a last slot with no lanes of this wave
+      A = B;
+      B = at(j + kc + 1);
+    }
+    j += kc;
+    __syncthreads();
+  }
+  j -= total;  // exactly one pass over the slots: keep j in [0, total)
+}
+
 // All sweeps of one work item: nsets sets of RW replicas, set k in the LDS rows
 // [k * n, (k + 1) * n).  Lane schedule streamed one slot ahead.  RD: every
 // graph of the run is FP32 on the grid schedule, so every operation of the
 // sweeps is exact and the step's sign comes from the parity form under
 // round-toward-minus-infinity.
-template <int ST, int W, bool RD>
+template <int ST, int W, bool RD, bool LAZY>
 __device__ void item_sweeps(uint32_t *lds, const GraphDev &g, const Item &it) {
   using F = Fmt<ST>;
   static_assert(!RD || ST == COSM_STORE_FP32, "the parity step is an FP32 grid form");
+  static_assert(!LAZY || RD, "FP32 wrapped at the twists is a grid form");
   // FP16 / BF16 / FP16_PK: wrapped at the twists only when the graph's drift bound holds
-  // (g.lazy, set by the host).  (FP32 on the grid could be too, exactly, but a
-  // second FP32 sweep path in this kernel made the mixed stream 5 % slower.)
+  // (g.lazy, set by the host).  FP32: a kernel of its own (LAZY), since a second
+  // sweep path in one kernel made the mixed stream 5 % slower.
   constexpr bool kLazyOk =
       ST == COSM_STORE_FP16 || ST == COSM_STORE_BF16 || ST == COSM_STORE_FP16_PK;
   constexpr int RW = W * F::kPerWord;
@@ -115,11 +234,17 @@ __device__ void item_sweeps(uint32_t *lds, const GraphDev &g, const Item &it) {
   const uint32_t set_bytes = (uint32_t)g.n * ROWB;
   const int nreps = nsets * RW;
   // reference angles of nch twists for the nreps replicas, then slots per class
-  float *theta_buf = reinterpret_cast<float *>(lds + (size_t)nsets * g.n * W);  // [nch][nreps]
+  const bool by_words = nsets == 1 && g.words != nullptr;
+  const int rows = g.n * nsets + (by_words ? kDummyRows : 0);
+  float *theta_buf = reinterpret_cast<float *>(lds + (size_t)rows * W);  // [nch][nreps]
   int32_t *Ks = reinterpret_cast<int32_t *>(theta_buf + 2 * kMaxSetReplicas);  // [C]
   const int nch = max(1, min(kThetaChunk, 2 * kMaxSetReplicas / nreps));
   int tw = 0;
-  for (int c = tid; c < g.C; c += nth) Ks[c] = as_global(g.Kc)[c];
+  for (int c = tid; c < g.C; c += nth) Ks[c] = as_global(by_words ? g.Kw : g.Kc)[c];
+  if (by_words && tid < kDummyRows) {
+    const uint32_t z[W] = {};
+    lds_store<W>(lds, g.n + tid, z);
+  }
 
   for (int s = tid; s < g.n * nsets; s += nth) {
     const int k = s / g.n, slot = s - k * g.n;
@@ -135,7 +260,13 @@ __device__ void item_sweeps(uint32_t *lds, const GraphDev &g, const Item &it) {
   }
   EdgeDesc dA{kEmptySlot, 0.0f}, dB{kEmptySlot, 0.0f};
   int jslot = 0;
-  if (g.total_slots > 0) {
+  su2 wA{}, wB{};
+  uint32_t jword = 0;
+  if (by_words) {
+    const __amdgpu_buffer_rsrc_t words = word_buffer(g.words, g.total_slots);
+    wA = __builtin_amdgcn_raw_buffer_load_b64(words, (uint32_t)tid * 8u, 0, 0);
+    wB = __builtin_amdgcn_raw_buffer_load_b64(words, (uint32_t)tid * 8u, kBatchThreads * 8, 0);
+  } else if (g.total_slots > 0) {
     const gptr<EdgeDesc> d0 = as_global(g.desc) + tid;
     const gptr<EdgeDesc> d1 = as_global(g.desc) + (size_t)(1 % g.total_slots) * nth + tid;
     dA = EdgeDesc{d0->slots, d0->J};
@@ -154,14 +285,20 @@ __device__ void item_sweeps(uint32_t *lds, const GraphDev &g, const Item &it) {
     chunk.get((t - 1) & 63u, alpha, twist);
     const float alpha_s = alpha * F::kStepScale;
     if (g.total_slots > 0) {
-      if (kLazyOk && g.lazy) {
+      if (by_words) {
+        word_classes<W>(g.words, Ks, g.C, g.total_slots, wA, wB, jword, alpha_s * g.jscale,
+                        [&](uint32_t(&u)[W], uint32_t(&v)[W], float aJ) {
+                          if (kLazyOk && g.lazy) update_words<ST, W, kLazyOk>(u, v, aJ);
+                          else update_words<ST, W, LAZY, RD>(u, v, aJ, pm);
+                        });
+      } else if (kLazyOk && g.lazy) {
         stream_classes(g.desc, Ks, g.C, g.total_slots, dA, dB, jslot, [&](const EdgeDesc &d) {
           edge_rows_sets<ST, W, kLazyOk>(lds, (d.slots & 0xffffu) * ROWB, (d.slots >> 16) * ROWB,
                                          set_bytes, nsets, alpha_s * d.J);
         });
       } else {
         stream_classes(g.desc, Ks, g.C, g.total_slots, dA, dB, jslot, [&](const EdgeDesc &d) {
-          edge_rows_sets<ST, W, false, RD>(lds, (d.slots & 0xffffu) * ROWB,
+          edge_rows_sets<ST, W, LAZY, RD>(lds, (d.slots & 0xffffu) * ROWB,
                                            (d.slots >> 16) * ROWB, set_bytes, nsets,
                                            alpha_s * d.J, pm);
         });
@@ -176,7 +313,8 @@ __device__ void item_sweeps(uint32_t *lds, const GraphDev &g, const Item &it) {
         __syncthreads();
       }
       tw++;
-      // set by set (no per-row division), two rows per thread in flight
+      // set by set (no per-row division), ROWS rows per thread in flight
+      constexpr int ROWS = 4;
       for (int k = 0; k < nsets; k++) {
         const float *cth = theta_buf + slot * nreps + k * RW;
         float ck[RW], tws[RW];
@@ -188,16 +326,16 @@ __device__ void item_sweeps(uint32_t *lds, const GraphDev &g, const Item &it) {
         TwistOps<ST, W> op;
         op.set(ck, tws, sc.win2);
         uint32_t *set = lds + (size_t)k * g.n * W;
-        for (int s0 = tid; s0 < g.n; s0 += 2 * nth) {
-          uint32_t w[2][W];
+        for (int s0 = tid; s0 < g.n; s0 += ROWS * nth) {
+          uint32_t w[ROWS][W];
 #pragma unroll
-          for (int q = 0; q < 2; q++)
+          for (int q = 0; q < ROWS; q++)
             if (s0 + q * nth < g.n) lds_load<W>(set, s0 + q * nth, w[q]);
 #pragma unroll
-          for (int q = 0; q < 2; q++) {
+          for (int q = 0; q < ROWS; q++) {
             if (s0 + q * nth < g.n) {
               if (kLazyOk && g.lazy) twist_row<ST, W, kLazyOk>(op, w[q]);
-              else op.apply(w[q]);
+              else twist_row<ST, W, LAZY>(op, w[q]);
               lds_store<W>(set, s0 + q * nth, w[q]);
             }
           }
@@ -219,11 +357,12 @@ __device__ void item_sweeps(uint32_t *lds, const GraphDev &g, const Item &it) {
     F::template unpack<W>(w, v);
 #pragma unroll
     for (int q = 0; q < RW; q++)
-      if (q < nvalid) F::store_elem(g.phases, base + q, kLazyOk && g.lazy ? F::wrap(v[q]) : v[q]);
+      if (q < nvalid)
+        F::store_elem(g.phases, base + q, LAZY || (kLazyOk && g.lazy) ? F::wrap(v[q]) : v[q]);
   }
 }
 
-template <int ST, bool RD>
+template <int ST, bool RD, bool LAZY>
 __global__ void __launch_bounds__(kBatchThreads) k_batch_sweeps(const GraphDev *__restrict__ graphs,
                                                                 const Item *__restrict__ items,
                                                                 RunDesc *rd) {
@@ -240,9 +379,9 @@ __global__ void __launch_bounds__(kBatchThreads) k_batch_sweeps(const GraphDev *
     if (k >= n_items) break;  // every wave of the workgroup leaves together
     const Item it = items[k];
     const GraphDev g = graphs[it.graph];  // by value: its fields stay in registers
-    if (g.W == 4) item_sweeps<ST, 4, RD>(lds, g, it);
-    else if (g.W == 2) item_sweeps<ST, 2, RD>(lds, g, it);
-    else item_sweeps<ST, 1, RD>(lds, g, it);
+    if (g.W == 4) item_sweeps<ST, 4, RD, LAZY>(lds, g, it);
+    else if (g.W == 2) item_sweeps<ST, 2, RD, LAZY>(lds, g, it);
+    else item_sweeps<ST, 1, RD, LAZY>(lds, g, it);
     __syncthreads();
   }
 }
@@ -333,10 +472,11 @@ struct cosm_batch {
   RunDesc *d_run = nullptr;
   int32_t *d_run_graphs = nullptr, *d_unit_prefix = nullptr;
   int64_t *d_phase_prefix = nullptr;
-  // the captured run, one per sweep variant (1: every graph FP32 on the grid)
-  hipGraph_t graph[2] = {nullptr, nullptr};
-  hipGraphExec_t exec[2] = {nullptr, nullptr};
-  int32_t run_rd = 0;       // the variant of the prepared run
+  // the captured run, one per sweep variant (1: every graph FP32 on the grid, 2: and
+  // within the drift bound of the wrap at the twists)
+  hipGraph_t graph[3] = {nullptr, nullptr, nullptr};
+  hipGraphExec_t exec[3] = {nullptr, nullptr, nullptr};
+  int32_t variant = 0;      // that of the prepared run
   hipEvent_t e0 = nullptr, e1 = nullptr;
   bool graphs_dirty = true;
 };
@@ -348,16 +488,16 @@ void enqueue_run(cosm_batch *b) {
   hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(64), 0, b->stream, b->d_run);
   hipLaunchKernelGGL((k_batch_init<ST>), dim3(2048), dim3(256), 0, b->stream, b->d_graphs,
                      b->d_run, b->d_run_graphs, b->d_phase_prefix);
+  const auto sweeps = [b](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(b->cus), dim3(kBatchThreads), (size_t)kLdsBudget, b->stream,
+                       b->d_graphs, b->d_items, b->d_run);
+  };
   if constexpr (ST == COSM_STORE_FP32) {
-    if (b->run_rd)
-      hipLaunchKernelGGL((k_batch_sweeps<ST, true>), dim3(b->cus), dim3(kBatchThreads),
-                         (size_t)kLdsBudget, b->stream, b->d_graphs, b->d_items, b->d_run);
-    else
-      hipLaunchKernelGGL((k_batch_sweeps<ST, false>), dim3(b->cus), dim3(kBatchThreads),
-                         (size_t)kLdsBudget, b->stream, b->d_graphs, b->d_items, b->d_run);
+    if (b->variant == 2) sweeps(k_batch_sweeps<ST, true, true>);
+    else if (b->variant == 1) sweeps(k_batch_sweeps<ST, true, false>);
+    else sweeps(k_batch_sweeps<ST, false, false>);
   } else {
-    hipLaunchKernelGGL((k_batch_sweeps<ST, false>), dim3(b->cus), dim3(kBatchThreads),
-                       (size_t)kLdsBudget, b->stream, b->d_graphs, b->d_items, b->d_run);
+    sweeps(k_batch_sweeps<ST, false, false>);
   }
   if (b->grouped)
     hipLaunchKernelGGL((k_batch_readout_group<ST>), dim3(2048),
@@ -371,24 +511,72 @@ void enqueue_run(cosm_batch *b) {
 
 template <int ST>
 void set_attrs(cosm_batch *b) {
-  (void)hipFuncSetAttribute((const void *)k_batch_sweeps<ST, false>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget);
-  if constexpr (ST == COSM_STORE_FP32)
-    (void)hipFuncSetAttribute((const void *)k_batch_sweeps<ST, true>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget);
+  const auto lds = [](const void *kernel) {
+    (void)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget);
+  };
+  lds((const void *)k_batch_sweeps<ST, false, false>);
+  if constexpr (ST == COSM_STORE_FP32) {
+    lds((const void *)k_batch_sweeps<ST, true, false>);
+    lds((const void *)k_batch_sweeps<ST, true, true>);
+  }
   (void)hipFuncSetAttribute(b->grouped ? (const void *)k_batch_readout_group<ST>
                                        : (const void *)k_batch_readout<ST>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->readout_lds);
+}
+
+// Whether rows of W words leave room for the word schedule's dummy rows, and J has one
+// magnitude.
+bool batch_words_apply(const cosm_state &s, int32_t C, int32_t W, size_t lds_budget) {
+  if (s.m == 0 ||
+      (size_t)(s.n + kDummyRows) * W * 4 + 2 * kMaxSetReplicas * 4 + (size_t)C * 4 > lds_budget)
+    return false;
+  const int32_t mag = std::abs(s.h_J[0]);
+  return mag != 0 && std::all_of(s.h_J.begin(), s.h_J.end(),
+                                 [mag](int32_t J) { return std::abs(J) == mag; });
+}
+
+// The lane schedule as word_classes reads it ([slot][lane][2]: u's byte offset with the
+// sign of J, v's byte offset); empty slots pair the dummy rows after the vertex rows.
+// Kw[c]: slots of class c | lanes holding entries in its last one << 16.
+void batch_words(const cosm_state &s, const LdsSchedule &L, int32_t W,
+                 std::vector<uint32_t> *words, std::vector<int32_t> *Kw) {
+  const uint32_t rowb = (uint32_t)(4 * W);
+  const size_t slots = (size_t)(L.total_slots + kStreamRepeat);
+  words->resize(slots * kBatchThreads * 2);
+  uint32_t *w = words->data();
+  const EdgeDesc *d = L.desc.data();
+  for (size_t j = 0; j < slots; j++)
+    for (uint32_t t = 0; t < kBatchThreads; t++, w += 2, d++) {
+      const bool any = d->slots != kEmptySlot;
+      const uint32_t u = any ? d->slots & 0xffffu : (uint32_t)s.n + t % 32u;
+      const uint32_t v = any ? d->slots >> 16 : (uint32_t)s.n + 32u + t % 32u;
+      w[0] = u * rowb | (any && d->J < 0.0f ? 0x80000000u : 0u);
+      w[1] = v * rowb;
+    }
+  Kw->assign((size_t)s.C, 0);
+  size_t j = 0;
+  for (int32_t c = 0; c < s.C; c++) {
+    const int32_t K = L.K[(size_t)c];
+    j += (size_t)K;
+    int32_t last = kBatchThreads;
+    while (K > 0 && last > 0 &&
+           L.desc[(j - 1) * kBatchThreads + (size_t)last - 1].slots == kEmptySlot)
+      last--;
+    (*Kw)[(size_t)c] = K | last << 16;
+  }
 }
 
 // The run's tables (work items, per-graph descriptors and prefix sums), on
 // the device and synchronised, for the graphs ids (valid ids of b->graphs).
 int prepare_run(cosm_batch *b, const std::vector<int32_t> &ids, bool fill = true) {
   const int32_t count = (int32_t)ids.size();
-  // the sweep variant: the parity form when every graph is FP32 on the grid
-  b->run_rd = b->storage == COSM_STORE_FP32 ? 1 : 0;
-  for (int32_t id : ids)
-    if (!b->graphs[(size_t)id]->dev.grid) b->run_rd = 0;
+  // the sweep variant: the parity form when every graph is FP32 on the grid, wrapped at
+  // the twists when every graph's drift allows it
+  b->variant = b->storage == COSM_STORE_FP32 ? 2 : 0;
+  for (int32_t id : ids) {
+    const BatchGraphHost &g = *b->graphs[(size_t)id];
+    b->variant = std::min(b->variant, !g.dev.grid ? 0 : wrap_at_twists(g.meta) ? 2 : 1);
+  }
   // work items: split every graph's replicas into items of up to sets_max sets,
   // shrinking the sets (fill) while the run would leave CUs without an item
   std::vector<int32_t> sets(ids.size());
@@ -433,7 +621,7 @@ int prepare_run(cosm_batch *b, const std::vector<int32_t> &ids, bool fill = true
     (void)hipFree(b->d_items);
     b->d_items = fresh;
     b->max_items = cap;
-    for (int v = 0; v < 2; v++) {
+    for (int v = 0; v < 3; v++) {
       if (b->exec[v]) (void)hipGraphExecDestroy(b->exec[v]);
       if (b->graph[v]) (void)hipGraphDestroy(b->graph[v]);
       b->exec[v] = nullptr;
@@ -660,7 +848,7 @@ int cosm_batch_destroy(cosm_batch *b) {
   clear_error();
   if (b == nullptr) return COSM_OK;
   (void)hipStreamSynchronize(b->stream);
-  for (int v = 0; v < 2; v++) {
+  for (int v = 0; v < 3; v++) {
     if (b->exec[v]) (void)hipGraphExecDestroy(b->exec[v]);
     if (b->graph[v]) (void)hipGraphDestroy(b->graph[v]);
   }
@@ -737,10 +925,12 @@ int cosm_batch_add_graph(cosm_batch *b, int32_t n, int64_t m, const int32_t *eu,
                                     ? "requested replicas per set do not fit one workgroup's LDS"
                                     : "graph does not fit one workgroup's LDS");
   std::vector<LdsSchedule> scheds(widths.size());
-  size_t desc_max = 0;
+  size_t desc_max = 0, words_max = 0;
   for (size_t k = 0; k < widths.size() && rc == COSM_OK; k++) {
     rc = build_lds_schedule(s, widths[k], kBatchThreads, &scheds[k]);
     desc_max = std::max(desc_max, scheds[k].desc.size());
+    if (batch_words_apply(s, num_colours, widths[k], b->lds_budget))
+      words_max = std::max(words_max, scheds[k].total_slots + (size_t)kStreamRepeat);
   }
   if (rc) {
     delete g;
@@ -764,6 +954,7 @@ int cosm_batch_add_graph(cosm_batch *b, int32_t n, int64_t m, const int32_t *eu,
     return at;
   };
   const size_t o_ph = take(nr * sb), o_desc = take(desc_max * sizeof(EdgeDesc)),
+               o_words = take(words_max * kBatchThreads * 8), o_Kw = take((size_t)num_colours * 4),
                o_K = take((size_t)num_colours * 4), o_sv = take((size_t)n * 4),
                o_eu = take((size_t)m * 4), o_ev = take((size_t)m * 4), o_J = take((size_t)m * 4),
                o_sp = take(nr), o_H = take((size_t)replicas * 8), o_cut = take((size_t)replicas * 8),
@@ -785,6 +976,8 @@ int cosm_batch_add_graph(cosm_batch *b, int32_t n, int64_t m, const int32_t *eu,
   d.desc = reinterpret_cast<const EdgeDesc *>(base + o_desc);
   d.Kc = reinterpret_cast<const int32_t *>(base + o_K);
   d.slot_vertex = reinterpret_cast<const int32_t *>(base + o_sv);
+  d.Kw = reinterpret_cast<const int32_t *>(base + o_Kw);
+  d.jscale = (float)max_abs_J;
   d.n = n;
   d.R = replicas;
   d.C = num_colours;
@@ -831,11 +1024,21 @@ int cosm_batch_add_graph(cosm_batch *b, int32_t n, int64_t m, const int32_t *eu,
     d.total_slots = s.lds.total_slots;
     g->sets_max = sets_for(W);
     up(o_desc, s.lds.desc.data(), s.lds.desc.size() * sizeof(EdgeDesc));
+    d.words = nullptr;
+    if (batch_words_apply(s, num_colours, W, b->lds_budget)) {
+      std::vector<uint32_t> words;
+      std::vector<int32_t> Kw;
+      batch_words(s, s.lds, W, &words, &Kw);
+      d.words = reinterpret_cast<const uint32_t *>(base + o_words);
+      up(o_words, words.data(), words.size() * 4);
+      up(o_Kw, Kw.data(), Kw.size() * 4);
+    }
     up(o_K, s.lds.K.data(), s.lds.K.size() * 4);
     up(o_sv, s.lds.slot_vertex.data(), s.lds.slot_vertex.size() * 4);
   };
-  install(0);
-  if (rc == COSM_OK && widths.size() > 1) {
+  if (widths.size() == 1) {
+    install(0);
+  } else if (rc == COSM_OK) {
     const int rt = tune_batch_graph(b, g, widths, install);
     if (rc == COSM_OK) rc = rt;  // (a failed upload inside install set rc itself)
   }
@@ -888,7 +1091,7 @@ int cosm_batch_run(cosm_batch *b, const int32_t *graph_ids, int32_t count) {
   for (int32_t id : ids)
     if (id < 0 || id >= (int32_t)b->graphs.size()) return set_error(COSM_EINVAL, "bad graph id");
   if (int rc = prepare_run(b, ids)) return rc;
-  const int v = b->run_rd;
+  const int v = b->variant;
   if (b->exec[v] == nullptr) {
     COSM_HIP_CHECK(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
     switch (b->storage) {
