@@ -36,10 +36,10 @@ VALU_PEAK_OPS = 256 * 64 * 2.4e9        # lane-ops per second, non-packed FP32
 
 # HBM bytes per launch of the sweep kernel at this workload, from rocprofv3
 # FETCH_SIZE and WRITE_SIZE (KiB per dispatch), each scaled by what the counter
-# reads for a 256 MiB device copy (FETCH_SIZE 131087 KiB -> x2.0; WRITE_SIZE
+# reads for a 256 MiB device copy (FETCH_SIZE 131088 KiB -> x2.0; WRITE_SIZE
 # 262144 KiB -> x1.0).  Valid only for the kernel sources they were taken on.
-TRAFFIC = dict(fetch_kib=1002863.8, write_kib=1295563.3, fetch_factor=2.0, write_factor=1.0,
-               sources_sha256="2fae1109e931794c28948c2b1b0b357f98e857ff7afc6988202b2461ab46c449")
+TRAFFIC = dict(fetch_kib=1033710.7, write_kib=1286286.4, fetch_factor=2.0, write_factor=1.0,
+               sources_sha256="b6f6b71eeebd6b76f06506d10039e010b4e7e1da23a3befb5c0f9cdc5dab8d1c")
 TRAFFIC_SOURCES = ('paper_2605_30355_amd/csrc/sweep_stream.hip', 'paper_2605_30355_amd/csrc/device_common.hpp', 'paper_2605_30355_amd/csrc/schedule.cpp', 'paper_2605_30355_amd/csrc/internal.hpp')
 
 

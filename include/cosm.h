@@ -80,15 +80,18 @@ enum { COSM_STORE_FP32 = 0, COSM_STORE_FP16 = 1, COSM_STORE_BF16 = 2, COSM_STORE
        COSM_STORE_FIX32 = 4, COSM_STORE_FP16_PK = 5 };
 /* Where a replica's phases live during a sweep.  LDS: a workgroup holds whole
  * replicas in LDS for all sweeps of a call.  HBM: phases stay in device memory,
- * one launch per colour class.  PLAIN: one replica per launch, one launch per
- * colour class (the unbatched baseline). */
+ * one launch per colour class (two per launch on graphs past the LDS, which then
+ * need a second phase buffer).  PLAIN: one replica per launch, one launch per
+ * colour class (the unbatched baseline).  AUTO: LDS where a replica fits (with
+ * FULL_GRADIENT where two copies of it do), else HBM. */
 enum { COSM_RES_AUTO = 0, COSM_RES_LDS = 1, COSM_RES_HBM = 2, COSM_RES_PLAIN = 3 };
 /* GRID: every phase, step and angle is a multiple of 2^-23 turn (2^-16 with
  * FIX16 storage), so sweeps are exact; the window must be a multiple of 2^-22
  * turn.  CONTINUOUS: the literal ramp alpha0 (S - t + 1) / S in FP32. */
 enum { COSM_SCHED_GRID = 0, COSM_SCHED_CONTINUOUS = 1 };
 /* Layout of the LDS form.  PAIR: every edge update reads and writes both
- * endpoint rows in LDS.  REGISTER: an independent set of vertices stays in
+ * endpoint rows in LDS (two colour classes per barrier on graphs of up to 1024
+ * vertices whose workgroups do not fill the GPU).  REGISTER: an independent set of vertices stays in
  * registers, a few per thread; each edge with an endpoint there is applied by
  * that endpoint's thread, which touches LDS only for the other endpoint (the
  * even tori: every edge), the remaining edges as in PAIR.  The same updates in
@@ -305,7 +308,8 @@ int cosm_batch_add_graph(cosm_batch *b, int32_t n, int64_t m, const int32_t *eu,
  * how it was chosen (tuned: 0 one width fits or was requested, 1 timed probes,
  * 2 the probe cache) with the chosen width's probe time (ms, one work item;
  * 0 when not probed), and lazy_wrap: 1 when its phases are wrapped at the
- * twists only (FP16 / BF16 / FP16_PK within the drift bound of cosm_info.lazy_wrap).
+ * twists only (FP16 / BF16 / FP16_PK within the drift bound of cosm_info.lazy_wrap;
+ * FP32 reports 0, also in runs that wrap it there, which changes no result).
  * Any output pointer may be NULL. */
 int cosm_batch_graph_shape(const cosm_batch *b, int32_t graph_id, int32_t *replicas_per_set,
                            int32_t *sets_per_item, int32_t *tuned, double *probe_ms,

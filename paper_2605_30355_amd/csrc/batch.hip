@@ -10,7 +10,8 @@
 //                    until the list is empty; a small graph packs several
 //                    replica sets into one workgroup's LDS so that every item
 //                    carries a similar amount of work;
-//   k_batch_readout  grid-stride over (graph, replica).
+//   k_batch_readout_group  (k_batch_readout past its limits) grid-stride over
+//                    (graph, group of replicas).
 // Kernel arguments only point at device tables that the host rewrites before
 // each run, so the three launches are captured once into a hipGraph and
 // replayed for every run.

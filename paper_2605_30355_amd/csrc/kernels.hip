@@ -4,10 +4,9 @@
 // wraps with v_fract_f32; FP16 / BF16 storage keeps the centred value
 // y = x - 1/2 in [-1/2, 1/2] and wraps with y - rint(y) (one more bit of
 // resolution than storing x); arithmetic is FP32 (FP16_PK: FP16, packed).
-// When no phase can drift by 1/2 turn between two twists, the 16-bit float
-// formats (every form) and FP32 (the
-// streamed LDS forms, grid schedule) wrap at the twists only (lazy16,
-// lds_lazy_wrap).  FIX16 storage keeps x as a
+// The 16-bit float formats wrap at the twists only when no phase can drift by
+// 1/2 turn between two of them (lazy16), FP32 on the grid schedule in the LDS
+// below one turn (wrap_at_twists).  FIX16 storage keeps x as a
 // 16-bit integer k (x = k 2^-16) and the LDS sweep updates it with packed
 // 16-bit integer ops (other forms go through FP32, exact on that grid).  On
 // the 2^-23 turn grid (2^-16 for FIX16) every add, subtract, fma by 2 and
