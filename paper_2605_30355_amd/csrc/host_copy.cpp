@@ -106,7 +106,8 @@ int copy_long(hipStream_t stream, Block *b, char *dst, const char *src, size_t b
   if (!emptied) return set_error(COSM_ENOMEM, "out of host memory");
   for (size_t c = 0; c < n; c++) emptied[c].store(0, std::memory_order_relaxed);
   auto part = [&](size_t c, int k, int of) {
-    const size_t l = len(c), p = (l / (size_t)of + 4095) / 4096 * 4096;
+    // (the share rounded up twice: to whole bytes, then to pages)
+    const size_t l = len(c), p = ((l + (size_t)of - 1) / (size_t)of + 4095) / 4096 * 4096;
     const size_t at = p * (size_t)k;
     if (at < l)
       std::memcpy(dst + c * kChunk + at, b->mem + (c % kChunks) * kChunk + at, std::min(p, l - at));
