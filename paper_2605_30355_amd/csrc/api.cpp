@@ -479,6 +479,7 @@ int init_state(cosm_state **out, int32_t n, int64_t m, const int32_t *eu, const 
   }
   if (h) s->h_h.assign(h, h + n);
   s->h_colour.assign(colour, colour + m);
+  find_wrap_bounds(s);
 
   // group the edges by class (stable): the plain / HBM arrays and LDS descriptors
   s->class_sizes.assign((size_t)num_colours, 0);

@@ -51,7 +51,10 @@ Key make_key(const cosm_state &s) {
   }
   const int32_t variant = (s.sched.grid ? 1 : 0) |
                           (s.sched.dwt_period > 0 && wrap_drift_turns(s) < 0.5 ? 2 : 0) |
-                          (wrap_at_twists(s) ? 4 : 0) | (wrap_at_sweeps(s) ? 8 : 0);
+                          (wrap_at_twists(s) ? 4 : 0) | (wrap_at_sweeps(s) ? 8 : 0) |
+                          (either_end_at_twists(s, true) ? 16 : 0) |
+                          (either_end_at_twists(s, false) ? 32 : 0) |
+                          (dual_wrap_at_sweeps(s) ? 64 : 0);
   return Key{s.n, s.m, s.C, s.R, s.p.storage, s.p.lds_form, s.has_h ? 1 : 0, variant, h};
 }
 

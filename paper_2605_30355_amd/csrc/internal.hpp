@@ -273,6 +273,10 @@ struct cosm_state {
   int64_t sumJ = 0;                 // sum of J over the edges
   int64_t sum_abs_J = 0;            // sum of |J|
   int64_t wdeg_max = 0;             // largest sum of |J| (and |h|) at one vertex
+  // differences taken from either end stay exact (find_wrap_bounds): over the sweeps
+  // between two twists and within one sweep in the two-class form, and between two
+  // twists for the register owners
+  bool dual_twists = false, dual_sweeps = false, owner_twists = false;
   size_t opt_temp_bytes = 0;        // segmented sort workspace (optimal readout)
   std::vector<int32_t> h_eu, h_ev, h_J, h_h, h_colour;
   std::vector<int32_t> h_slot;       // h of the vertex in each LDS slot (host copy)
@@ -340,9 +344,16 @@ bool grid_parity_step(const cosm_state &s);
 double wrap_drift_turns(const cosm_state &s);
 // Whether the FP32 LDS sweeps under the parity step may leave the wrap of every
 // update to the twists: drift below one whole turn and phases on the grid
-// (kernels.hip).  Wider than lds_lazy_wrap's half turn, which also bounds the
+// (wrap_bound.cpp).  Wider than lds_lazy_wrap's half turn, which also bounds the
 // forms without the parity step and is what cosm_info.lazy_wrap reports.
 bool wrap_at_twists(const cosm_state &s);
+// The same for the forms that take an edge's difference from either of its ends
+// (dual: the two-class form, else the streamed register owners), which also need it
+// below two turns, and the two-class form's for a wrap at the end of every sweep;
+// find_wrap_bounds fills in the state's part of these, once it has its schedule.
+bool either_end_at_twists(const cosm_state &s, bool dual);
+bool dual_wrap_at_sweeps(const cosm_state &s);
+void find_wrap_bounds(cosm_state *s);
 // The same bound for a wrap at the end of every sweep, and, for any update, FP32
 // phases on the grid whose drift within one sweep stays below a turn.
 bool wrap_at_sweeps(const cosm_state &s);

@@ -813,53 +813,6 @@ bool lds_twist_fused(const cosm_state &s) {
   return slots > kRegisterSlotsMax;
 }
 
-namespace {
-// The largest step and twist in turns (grid: exact products of small integers
-// and powers of two).
-double alpha_max_turns(const Schedule &sc) {
-  return sc.grid ? (double)sc.a0_units * (double)sc.aunit : (double)sc.alpha0_turns;
-}
-double twist_max_turns(const Schedule &sc) {
-  return sc.grid ? (double)sc.twist_num2 * (double)sc.a0_units * (double)sc.tunit
-                 : (double)sc.dwt_ratio * alpha_max_turns(sc);
-}
-}  // namespace
-
-double wrap_drift_turns(const cosm_state &s) {
-  // the largest drift of one phase from its wrapped range between two twists:
-  // the twist left unwrapped plus every step of `period` sweeps, J and h alike
-  return twist_max_turns(s.sched) +
-         (double)s.sched.dwt_period * alpha_max_turns(s.sched) * (double)s.wdeg_max;
-}
-
-bool exact_grid_fp32(const cosm_state &s) {
-  return s.p.storage == COSM_STORE_FP32 && s.sched.grid && s.p.update == COSM_UPDATE_SCS;
-}
-
-// Between two twists a phase starts in [0, 1 + twist) and moves by at most
-// period x alpha0 x (largest sum of |J| and |h| at one vertex); with that drift
-// below one turn it stays in (-1, 2), where every multiple of 2^-23 turn is an
-// FP32 number, so the phases and the updates stay exact without a wrap.  The
-// difference x_u - x_v may then reach 3 turns in magnitude and round, but
-// toward minus infinity, and halves of turns are FP32 numbers, so
-// floor(2(x_u - x_v)) and with it the step's sign are still exact.  The twist
-// wraps before it tests its windows.  (The forms without the parity step need
-// the difference itself exact: half a turn, lds_lazy_wrap.)  Two of seven VALU
-// per update fewer; whole trials, wrapping after every update -> at the twists:
-// 20x20 torus, 64 replicas x 2000 sweeps 1057 -> 956 us (latency); 3-regular,
-// N = 2000, 1024 x 10^4 10.79 -> 10.52 ms and 5-regular, N = 20000, 2048 x 1000
-// 42.0 -> 41.0 ms (LDS).
-bool wrap_at_twists(const cosm_state &s) {
-  return exact_grid_fp32(s) && s.on_grid && s.sched.dwt_period > 0 && wrap_drift_turns(s) < 1.0;
-}
-
-// The same with a wrap at the end of every sweep.
-bool grid_drift_below_turn(const cosm_state &s) {
-  return s.p.storage == COSM_STORE_FP32 && s.sched.grid && s.on_grid &&
-         twist_max_turns(s.sched) + alpha_max_turns(s.sched) * (double)s.wdeg_max < 1.0;
-}
-bool wrap_at_sweeps(const cosm_state &s) { return exact_grid_fp32(s) && grid_drift_below_turn(s); }
-
 bool grid_parity_step(const cosm_state &s) {
   const int32_t st = s.p.storage;
   return (st == COSM_STORE_FP32 || st == COSM_STORE_FP16 || st == COSM_STORE_BF16) &&

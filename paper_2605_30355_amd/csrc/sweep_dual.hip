@@ -32,18 +32,19 @@ namespace cosm {
 namespace {
 
 // When phases are wrapped (FP32 on the grid schedule, as in wrap_at_twists: exact
-// while every phase stays in (-1, 2)).
+// while every phase stays in (-1, 2) and the difference that either end takes of an
+// edge of the first class below two turns).
 enum Wrap {
   kWrapUpdates = 0,  // after every update (and always by the fixed-point formats)
-  kWrapSweeps = 1,   // in the last round of a sweep: one sweep's steps and the
-                     // twist stay below a turn
-  kWrapTwists = 2    // at the twists (wrap_at_twists)
+  kWrapSweeps = 1,   // in the last round of a sweep (dual_wrap_at_sweeps)
+  kWrapTwists = 2    // at the twists (either_end_at_twists)
 };
 
 // Class c on one endpoint: row r moves as the endpoint of its edge to row w
 // (left as it is).  FP32: aJ carries the sign of the role, two is +2 where r is
-// the edge's u and -2 where it is v; the fixed-point formats take the role as
-// flip.  The pair update's r bit for bit (update_reg_words).
+// the edge's u and -2 where it is v (the difference exact, either_end_at_twists);
+// the fixed-point formats take the role as flip.  The pair update's r bit for bit
+// (update_reg_words).
 template <int ST, int W, bool WRAP>
 __device__ __forceinline__ void update_end(uint32_t (&r)[W], const uint32_t (&w)[W], float aJ,
                                            uint32_t role, float pm) {
@@ -236,8 +237,8 @@ template <int W>
 int launch_w(cosm_state *s, const LdsArgs &a) {
   switch (s->p.storage) {
     case COSM_STORE_FP32:
-      if (wrap_at_twists(*s)) return launch_r<COSM_STORE_FP32, W, kWrapTwists>(s, a);
-      if (wrap_at_sweeps(*s)) return launch_r<COSM_STORE_FP32, W, kWrapSweeps>(s, a);
+      if (either_end_at_twists(*s, true)) return launch_r<COSM_STORE_FP32, W, kWrapTwists>(s, a);
+      if (dual_wrap_at_sweeps(*s)) return launch_r<COSM_STORE_FP32, W, kWrapSweeps>(s, a);
       return launch_r<COSM_STORE_FP32, W, kWrapUpdates>(s, a);
     case COSM_STORE_FIX32: return launch_r<COSM_STORE_FIX32, W, kWrapUpdates>(s, a);
     case COSM_STORE_FIX16: return launch_r<COSM_STORE_FIX16, W, kWrapUpdates>(s, a);

@@ -67,7 +67,8 @@ struct RStreamArgs {
 // moves by -D and the LDS row by +D, D = +-aJf.  LAZY: no wrap (FP32 phases
 // wrapped at the twists only, as in the streamed pair form; the grid schedule,
 // so the sweeps run under f32_round_down and the sign comes from the parity of
-// floor(2e), the flip folded into the fma's factor -2).
+// floor(2e), the flip folded into the fma's factor -2: x_r - x_w must be exact,
+// either_end_at_twists).
 template <int ST, int W, bool LAZY>
 __device__ __forceinline__ void update_owner(uint32_t (&r)[W], uint32_t (&w)[W], float aJf,
                                              uint32_t fm, float pm) {
@@ -392,7 +393,7 @@ int launch_sweeps_rstream(cosm_state *s, int64_t n_sweeps) {
   a.k1 = (uint32_t)(s->seed >> 32);
   a.rid0 = (uint32_t)s->rid0;
   const int W = s->shape.rw;  // FP32: one word per replica
-  if (lds_lazy_wrap(*s) || wrap_at_twists(*s))
+  if (lds_lazy_wrap(*s) || either_end_at_twists(*s, false))
     return launch_rstream_l<COSM_STORE_FP32, true>(s, a, W, L.reg_k);
   return launch_rstream_l<COSM_STORE_FP32, false>(s, a, W, L.reg_k);
 }
