@@ -466,6 +466,7 @@ int build_reg_impl(const cosm_state &s, const RegOptions &o, LdsSchedule *out) {
       for (const Adj &a : adj[(size_t)v])
         if (!rclass[(size_t)a.cls]) solo_class[(size_t)a.cls] = 1;
   for (int32_t c = 0; c < C; c++) {
+    // (solo edges take the last pair slot's place)
     if ((int64_t)free_edges[(size_t)c].size() > (int64_t)(P - solo_class[(size_t)c]) * nth)
       return set_error(COSM_ERANGE, "too many edges outside the register set");
     if (!free_edges[(size_t)c].empty()) reg_free = 1;
@@ -487,7 +488,8 @@ int build_reg_impl(const cosm_state &s, const RegOptions &o, LdsSchedule *out) {
     std::vector<int32_t> &list = free_edges[(size_t)c];
     std::vector<uint8_t> done(list.size(), 0);
     size_t left = list.size();
-    for (int32_t ps = 0; ps < P && left > 0; ps++) {
+    const int32_t slots = P - solo_class[(size_t)c];
+    for (int32_t ps = 0; ps < slots && left > 0; ps++) {
       const size_t cp = (size_t)c * P + ps;
       for (int32_t tg = 0; tg < groups_per_k && left > 0; tg++) {
         for (int32_t p = 0; p < G && left > 0; p++) {
@@ -527,7 +529,7 @@ int build_reg_impl(const cosm_state &s, const RegOptions &o, LdsSchedule *out) {
     for (size_t i = 0; i < list.size(); i++) {
       if (done[i]) continue;
       size_t at = (size_t)c * P * nth;
-      while (free_at[at] >= 0) at++;  // fits: at most P nth edges
+      while (free_at[at] >= 0) at++;  // fits: at most slots x nth edges
       const int32_t e = list[i];
       free_at[at] = e;
       const size_t cp = at / (size_t)nth;
