@@ -79,9 +79,9 @@ MemPlan plan_memory(int32_t n, int64_t m, int32_t C, int32_t R, const cosm_param
   mp.inc_off = take(fg ? ((size_t)n + 1) * 4 : 0);
   mp.inc_nbr = take(fg ? (size_t)(2 * m) * 4 : 0);
   mp.inc_J = take(fg ? (size_t)(2 * m) * 4 : 0);
-  const bool dual = dual_hbm_form(n, C, R, p);
+  const bool dual = dual_hbm_form(n, m, C, R, p);
   mp.phases_alt = take(fg || dual ? nr * storage_bytes(p.storage) : 0);
-  mp.dual_entries = take(dual ? dual_hbm_entry_bytes(n, C) : 0);
+  mp.dual_entries = take(dual ? dual_hbm_entry_bytes(n, m, C) : 0);
   mp.dual_theta = take(dual ? (size_t)R * 4 : 0);
   const bool opt = p.readout == COSM_READOUT_OPTIMAL;
   mp.opt_keys = take(opt ? nr * 4 : 0);
@@ -604,7 +604,7 @@ int init_state(cosm_state **out, int32_t n, int64_t m, const int32_t *eu, const 
   rc = rc ? rc : up(d.peu, peu.data(), (size_t)m * 4);
   rc = rc ? rc : up(d.pev, pev.data(), (size_t)m * 4);
   rc = rc ? rc : up(d.pJ, pJ.data(), (size_t)m * 4);
-  if (s->shape.residency == COSM_RES_HBM && dual_hbm_form(n, num_colours, replicas, s->p))
+  if (s->shape.residency == COSM_RES_HBM && dual_hbm_form(n, m, num_colours, replicas, s->p))
     rc = rc ? rc : upload_dual_hbm(s);
   if (s->p.update == COSM_UPDATE_FULL_GRADIENT) {
     rc = rc ? rc : up(d.inc_off, inc_off.data(), inc_off.size() * 4);

@@ -289,7 +289,10 @@ struct cosm_state {
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   // device whose static scratch array holds the buffers (cosm_init_static), or -1
   int32_t static_dev = -1;
-  std::vector<int32_t> dual_count;  // two-class device-memory form: entries of each round
+  // two-class device-memory form: entries of each round, and whether it is a pass on
+  // every sweep; empty where no round is
+  std::vector<int32_t> dual_count;
+  std::vector<uint8_t> dual_pays;
 };
 
 namespace cosm {
@@ -362,8 +365,9 @@ bool grid_drift_below_turn(const cosm_state &s);
 // evaluates them.
 float host_alpha(const Schedule &sc, int64_t t);
 float host_twist(const Schedule &sc, int64_t t);
-// The device-memory forms' field sub-sweep and twist on replicas [rbeg, rbeg +
-// rcount), and the replicas per lane their accesses can take.
+// The device-memory forms' class, field sub-sweep and twist on replicas [rbeg, rbeg +
+// rcount), in place, and the replicas per lane their accesses can take.
+int launch_class_hbm(cosm_state *s, int32_t c, float alpha, int32_t rbeg, int32_t rcount);
 int launch_field_hbm(cosm_state *s, float alpha, int32_t rbeg, int32_t rcount);
 int launch_dwt_hbm(cosm_state *s, int64_t t, int32_t rbeg, int32_t rcount);
 int hbm_vec(int32_t R, int32_t rbeg, int32_t rcount);
@@ -390,18 +394,20 @@ int launch_sweeps_stream(cosm_state *s, int64_t n_sweeps);
 // An entry of the two-class forms (sweep_dual.hip, sweep_dual_hbm.hip): an edge
 // (u, v) of the round's second class (v = -1, J = 0 where a vertex has none) and the
 // first class's edges at u and v (partner -1 for none; f: the endpoint is that
-// edge's v).  A round's entries cover every vertex once.
+// edge's v).  A round's entries cover every vertex once; rounds that wanted (null: all)
+// leaves out have none.
 struct DualEntry {
   int32_t u, v, pu, pv;
   int32_t J, Ju, Jv;
   int32_t fu, fv;
 };
-std::vector<std::vector<DualEntry>> dual_entries(const cosm_state &s);
+std::vector<std::vector<DualEntry>> dual_entries(const cosm_state &s,
+                                                 const std::vector<uint8_t> *wanted = nullptr);
 // The device-memory sweeps two classes at a time (sweep_dual_hbm.hip): whether a
-// state of these sizes takes them (it then has a second phase buffer and the
+// state of these sizes may take them (it then has a second phase buffer and the
 // entries in device memory), and its launcher.
-bool dual_hbm_form(int32_t n, int32_t C, int32_t R, const cosm_params &p);
-size_t dual_hbm_entry_bytes(int32_t n, int32_t C);
+bool dual_hbm_form(int32_t n, int64_t m, int32_t C, int32_t R, const cosm_params &p);
+size_t dual_hbm_entry_bytes(int32_t n, int64_t m, int32_t C);
 int upload_dual_hbm(cosm_state *s);
 int launch_sweeps_dual_hbm(cosm_state *s, int64_t n_sweeps);
 // Two-class form (sweep_dual.hip; small graphs): its schedule for rows of W

@@ -301,18 +301,19 @@ __global__ void __launch_bounds__(1024) k_sweep_lds(const LdsArgs a) {
 // ---------------------------------------------------------------------------
 // Device-memory forms: one launch per colour class.  HBM form: a wave covers
 // 64 VEC consecutive replicas of one edge (coalesced rows of the [n][R]
-// layout, VEC per lane).  PLAIN form: one replica, a thread per edge.
+// layout, VEC per lane; replicas [rbeg, rend)).  PLAIN form: one replica, a thread per edge.
 // ---------------------------------------------------------------------------
 template <int ST, int VEC>
 __global__ void __launch_bounds__(256) k_class_hbm(void *phases, const int32_t *peu,
                                                    const int32_t *pev, const float *pJ,
                                                    int32_t beg, int32_t cnt, int32_t R,
-                                                   int32_t rchunks, float alpha, int32_t lazy) {
+                                                   int32_t rbeg, int32_t rend, int32_t rchunks,
+                                                   float alpha, int32_t lazy) {
   const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int lane = threadIdx.x & 63;
   const int64_t e = wave / rchunks;
-  const int32_t r = ((int32_t)(wave % rchunks) * 64 + lane) * VEC;
-  if (e >= cnt || r >= R) return;
+  const int32_t r = rbeg + ((int32_t)(wave % rchunks) * 64 + lane) * VEC;
+  if (e >= cnt || r >= rend) return;
   const int32_t u = peu[beg + e], v = pev[beg + e];
   const float aJ = alpha * pJ[beg + e];
   float xu[VEC], xv[VEC];
@@ -622,19 +623,29 @@ int field_hbm_st(cosm_state *s, float alpha, int32_t rbeg, int32_t rcount) {
 }
 
 template <int ST, int VEC>
-int class_hbm_vec(cosm_state *s, int32_t beg, int32_t cnt, float alpha) {
-  const int32_t rchunks = (s->R + 64 * VEC - 1) / (64 * VEC);
+int class_hbm_vec(cosm_state *s, int32_t c, float alpha, int32_t rbeg, int32_t rcount) {
+  const int32_t beg = s->class_begin[(size_t)c], cnt = s->class_sizes[(size_t)c];
+  if (cnt == 0) return COSM_OK;
+  const int32_t rchunks = (rcount + 64 * VEC - 1) / (64 * VEC);
   const int64_t threads = (int64_t)cnt * rchunks * 64;
   hipLaunchKernelGGL((k_class_hbm<ST, VEC>), dim3((unsigned)((threads + 255) / 256)), dim3(256),
-                     0, s->stream, s->d.phases, s->d.peu, s->d.pev, s->d.pJ, beg, cnt, s->R,
-                     rchunks, alpha, (int32_t)lazy16(*s));
+                     0, s->stream, s->d.phases, s->d.peu, s->d.pev, s->d.pJ, beg, cnt, s->R, rbeg,
+                     rbeg + rcount, rchunks, alpha, (int32_t)lazy16(*s));
   return launch_check("k_class_hbm");
+}
+
+template <int ST>
+int class_hbm_st(cosm_state *s, int32_t c, float alpha, int32_t rbeg, int32_t rcount) {
+  switch (hbm_vec(s->R, rbeg, rcount)) {
+    case 4: return class_hbm_vec<ST, 4>(s, c, alpha, rbeg, rcount);
+    case 2: return class_hbm_vec<ST, 2>(s, c, alpha, rbeg, rcount);
+    default: return class_hbm_vec<ST, 1>(s, c, alpha, rbeg, rcount);
+  }
 }
 
 template <int ST>
 int sweeps_hbm_st(cosm_state *s, int64_t n_sweeps) {
   const Schedule &sc = s->sched;
-  const int vec = hbm_vec(s->R, 0, s->R);
   for (int64_t t = s->t + 1; t <= s->t + n_sweeps; t++) {
     const float alpha = host_alpha(sc, t);
     if (s->p.update == COSM_UPDATE_FULL_GRADIENT) {
@@ -645,14 +656,8 @@ int sweeps_hbm_st(cosm_state *s, int64_t n_sweeps) {
       if (int rc = launch_check("k_full_gradient")) return rc;
       std::swap(s->d.phases, s->d.phases_alt);
     } else {
-      for (int c = 0; c < s->C; c++) {
-        const int32_t beg = s->class_begin[c], cnt = s->class_sizes[c];
-        if (cnt == 0) continue;
-        const int rc = vec == 4   ? class_hbm_vec<ST, 4>(s, beg, cnt, alpha)
-                       : vec == 2 ? class_hbm_vec<ST, 2>(s, beg, cnt, alpha)
-                                  : class_hbm_vec<ST, 1>(s, beg, cnt, alpha);
-        if (rc) return rc;
-      }
+      for (int c = 0; c < s->C; c++)
+        if (int rc = class_hbm_st<ST>(s, c, alpha, 0, s->R)) return rc;
       if (s->has_h)
         if (int rc = field_hbm_st<ST>(s, alpha, 0, s->R)) return rc;
     }
@@ -846,6 +851,11 @@ int lds_capacity_bytes() {
 }
 
 namespace {
+template <int ST> struct ClassHbmFn {
+  static int run(cosm_state *s, int32_t c, float alpha, int32_t rbeg, int32_t rcount) {
+    return class_hbm_st<ST>(s, c, alpha, rbeg, rcount);
+  }
+};
 template <int ST> struct FieldHbmFn {
   static int run(cosm_state *s, float alpha, int32_t rbeg, int32_t rcount) {
     return field_hbm_st<ST>(s, alpha, rbeg, rcount);
@@ -857,6 +867,9 @@ template <int ST> struct DwtHbmFn {
   }
 };
 }  // namespace
+int launch_class_hbm(cosm_state *s, int32_t c, float alpha, int32_t rbeg, int32_t rcount) {
+  return dispatch_storage<ClassHbmFn>(s->p.storage, s, c, alpha, rbeg, rcount);
+}
 int launch_field_hbm(cosm_state *s, float alpha, int32_t rbeg, int32_t rcount) {
   return dispatch_storage<FieldHbmFn>(s->p.storage, s, alpha, rbeg, rcount);
 }

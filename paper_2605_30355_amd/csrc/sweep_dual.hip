@@ -268,7 +268,8 @@ bool dual_form_default(const cosm_state &s, int32_t W, int32_t blocks, int32_t c
 // The entries of every round.  Round q holds classes 2q and 2q + 1 (an odd last
 // class alone), entries in order of their first vertex, so that on lattices
 // neighbouring lanes or waves read neighbouring rows.
-std::vector<std::vector<DualEntry>> dual_entries(const cosm_state &s) {
+std::vector<std::vector<DualEntry>> dual_entries(const cosm_state &s,
+                                                 const std::vector<uint8_t> *wanted) {
   const int32_t n = s.n, C = s.C, rounds = (C + 1) / 2;
   // edge of each vertex in a class
   std::vector<int32_t> e0((size_t)n), e1((size_t)n);
@@ -284,9 +285,10 @@ std::vector<std::vector<DualEntry>> dual_entries(const cosm_state &s) {
     }
   };
   std::vector<std::vector<DualEntry>> out((size_t)rounds);
-  for (auto &l : out) l.reserve((size_t)n / 2 + 1);
   std::vector<uint8_t> done((size_t)n);
   for (int32_t q = 0; q < rounds; q++) {
+    if (wanted != nullptr && !(*wanted)[(size_t)q]) continue;
+    out[(size_t)q].reserve((size_t)n / 2 + 1);
     edges_of(2 * q, e0);
     edges_of(2 * q + 1, e1);
     std::fill(done.begin(), done.end(), 0);

@@ -19,6 +19,10 @@
 // 11.7 ms (12.8 without the groups), FIX16 11.7 -> 9.4; 3-regular graph of 60000, whose
 // partners lie anywhere, 11.7 -> 10.7.  It is bound by the caches and device memory:
 // two reads and a write of every row per pass at some 9 TB/s.
+//
+// A pass moves every row, also where few have an edge; rounds of small classes run
+// class by class in place instead (round_pays), the last one on sweeps without a twist
+// only: a twist of its own moves every row too.
 #include <hip/hip_runtime.h>
 
 #include <string>
@@ -134,11 +138,19 @@ int checked(const char *what) {
   return COSM_OK;
 }
 
+// Whether classes of a and b edges are worth a pass: it reads and writes n rows, and
+// reads the 2a partners' (from the caches); one class after the other reads and
+// writes 2(a + b).
+// Two such rounds on 60000 vertices, random partners, 1024 replicas, classes -> passes
+// in us a sweep, at a + 2b = 0.6 n: FP32 134 -> 191, FIX16 76 -> 95; 0.9 n: 191 -> 205,
+// 103 -> 107; 1.05 n: 219 -> 211, 117 -> 112; 1.5 n: 303 -> 230, 159 -> 131.  Lattice
+// neighbours and fewer replicas gain from 0.7 n on (FP32, 32 replicas 33 -> 21).
+bool round_pays(int32_t n, int64_t a, int64_t b) { return a + 2 * b > n; }
+
 template <int ST, int VEC>
 int pass(cosm_state *s, int32_t q, const Entry *entries, int32_t rbeg, int32_t rend, float alpha,
          const float *theta, float twist) {
   const int32_t count = s->dual_count[(size_t)q];
-  if (count == 0) return COSM_OK;
   const int64_t waves = (int64_t)count * ((rend - rbeg + 64 * VEC - 1) / (64 * VEC));
   const dim3 grid((unsigned)((waves + 3) / 4)), block(256);
   if (lazy16(*s))
@@ -180,6 +192,12 @@ int sweeps(cosm_state *s, int64_t n_sweeps) {
       }
       const Entry *entries = static_cast<const Entry *>(s->d.dual_entries);
       for (int32_t q = 0; q < rounds; q++) {
+        if (!s->dual_pays[(size_t)q] && !(fused && q == rounds - 1)) {
+          for (int32_t c = 2 * q; c < std::min(s->C, 2 * q + 2); c++)
+            if (int rc = launch_class_hbm(s, c, alpha, rbeg, rend - rbeg)) return rc;
+          entries += s->dual_count[(size_t)q];
+          continue;
+        }
         const float *theta = fused && q == rounds - 1 ? s->d.dual_theta : nullptr;
         const float twist = host_twist(sc, t);
         const int rc = vec == 4   ? pass<ST, 4>(s, q, entries, rbeg, rend, alpha, theta, twist)
@@ -189,11 +207,10 @@ int sweeps(cosm_state *s, int64_t n_sweeps) {
         entries += s->dual_count[(size_t)q];
         std::swap(s->d.phases, s->d.phases_alt);
       }
-      if (s->has_h) {
+      if (s->has_h)
         if (int rc = launch_field_hbm(s, alpha, rbeg, rend - rbeg)) return rc;
-        if (twist_now)
-          if (int rc = launch_dwt_hbm(s, t, rbeg, rend - rbeg)) return rc;
-      }
+      if (twist_now && !fused)
+        if (int rc = launch_dwt_hbm(s, t, rbeg, rend - rbeg)) return rc;
     }
     rbeg = rend;
   }
@@ -202,28 +219,40 @@ int sweeps(cosm_state *s, int64_t n_sweeps) {
 
 }  // namespace
 
-bool dual_hbm_form(int32_t n, int32_t C, int32_t R, const cosm_params &p) {
+bool dual_hbm_form(int32_t n, int64_t m, int32_t C, int32_t R, const cosm_params &p) {
   const size_t elem = p.storage == COSM_STORE_FP32 || p.storage == COSM_STORE_FIX32 ? 4 : 2;
-  return n >= kVerticesMin && C >= 2 && p.update == COSM_UPDATE_SCS &&
+  return n >= kVerticesMin && dual_hbm_entry_bytes(n, m, C) > 0 && p.update == COSM_UPDATE_SCS &&
          (p.residency == COSM_RES_AUTO || p.residency == COSM_RES_HBM) &&
          (size_t)n * (size_t)R * elem <= kAltBytesMax;
 }
 
-size_t dual_hbm_entry_bytes(int32_t n, int32_t C) {
-  // (a round has at most one entry per vertex, two vertices to most of them)
-  return (size_t)((C + 1) / 2) * ((size_t)n / 2 + 1) * sizeof(Entry);
+size_t dual_hbm_entry_bytes(int32_t n, int64_t m, int32_t C) {
+  // two classes that pay have at least (n + 1) / 2 edges (round_pays; b <= n / 2); with
+  // them the last round, for the twist.  A round has an entry for two vertices, and one
+  // for an odd one.
+  const int64_t pay = std::min<int64_t>(C / 2, 2 * m / ((int64_t)n + 1));
+  if (pay == 0) return 0;
+  return (size_t)std::min<int64_t>((C + 1) / 2, pay + 1) * ((size_t)n / 2 + 1) * sizeof(Entry);
 }
 
 int upload_dual_hbm(cosm_state *s) {
+  std::vector<uint8_t> pays((size_t)(s->C + 1) / 2, 0);
+  bool any = false;
+  for (int32_t q = 0; 2 * q + 1 < s->C; q++) {
+    pays[(size_t)q] = round_pays(s->n, s->class_sizes[(size_t)2 * q], s->class_sizes[(size_t)2 * q + 1]);
+    any = any || pays[(size_t)q];
+  }
+  if (!any) return COSM_OK;
+  s->dual_pays = pays;
+  if (s->sched.dwt_period > 0 && !s->has_h) pays.back() = 1;
   std::vector<Entry> all;
-  all.reserve(dual_hbm_entry_bytes(s->n, s->C) / sizeof(Entry));
-  for (const auto &round : dual_entries(*s)) {
+  for (const auto &round : dual_entries(*s, &pays)) {
     s->dual_count.push_back((int32_t)round.size());
     for (const DualEntry &e : round)
       all.push_back(Entry{e.u, e.v, e.pu, e.pv, (float)e.J, (float)e.Ju, (float)e.Jv,
                           e.fu | e.fv << 1});
   }
-  if (all.size() * sizeof(Entry) > dual_hbm_entry_bytes(s->n, s->C))
+  if (all.size() * sizeof(Entry) > dual_hbm_entry_bytes(s->n, s->m, s->C))
     return set_error(COSM_ERANGE, "internal error: entries past their buffer");
   COSM_HIP_CHECK(hipMemcpyAsync(s->d.dual_entries, all.data(), all.size() * sizeof(Entry),
                                 hipMemcpyHostToDevice, s->stream));
