@@ -164,6 +164,15 @@ int pass(cosm_state *s, int32_t q, const Entry *entries, int32_t rbeg, int32_t r
   return checked("k_dual_hbm");
 }
 
+// Passes in sweeps t + 1 .. t + n (those of the last round on twist sweeps among them).
+int64_t passes_in(const cosm_state &s, int64_t t, int64_t n) {
+  int64_t each = 0;
+  for (uint8_t p : s.dual_pays) each += p;
+  const int64_t period = s.sched.dwt_period;
+  const int64_t twists = period > 0 && !s.has_h ? (t + n) / period - t / period : 0;
+  return each * n + (s.dual_pays.back() ? 0 : twists);
+}
+
 template <int ST>
 int sweeps(cosm_state *s, int64_t n_sweeps) {
   const Schedule &sc = s->sched;
@@ -172,44 +181,56 @@ int sweeps(cosm_state *s, int64_t n_sweeps) {
   const size_t row = (size_t)2 * s->n * (4 / Fmt<ST>::kPerWord);
   int64_t group = (int64_t)(kGroupBytes / row) / 256 * 256;
   group = std::max<int64_t>(256, group);
-  void *const first = s->d.phases, *const second = s->d.phases_alt;
+  // A call leaves the phases in the buffer it found them in: one that is captured into a
+  // graph keeps its buffers, whatever calls run between the graph's replays.  An odd
+  // number of passes becomes even by one round that runs class by class.
+  const bool odd = passes_in(*s, s->t, n_sweeps) % 2 != 0;
+  struct Buffers {
+    DeviceBuffers &d;
+    void *const first = d.phases, *const second = d.phases_alt;
+    ~Buffers() {  // (on an error between two passes too)
+      d.phases = first;
+      d.phases_alt = second;
+    }
+  } const buffers{s->d};
   for (int32_t rbeg = 0; rbeg < s->R;) {
     int32_t rend = (int32_t)std::min<int64_t>(s->R, rbeg + group);
     if (s->R - rend < group / 2) rend = s->R;  // no small last group
     const int vec = hbm_vec(s->R, rbeg, rend - rbeg);
-    s->d.phases = first;
-    s->d.phases_alt = second;
+    bool drop = odd;  // a pass to leave out
     for (int64_t t = s->t + 1; t <= s->t + n_sweeps; t++) {
-      const float alpha = host_alpha(sc, t);
+      const float alpha = host_alpha(sc, t), twist = host_twist(sc, t);
       const bool twist_now = sc.dwt_period > 0 && t % sc.dwt_period == 0;
-      const bool fused = twist_now && !s->has_h;
-      if (fused) {
-        hipLaunchKernelGGL(k_theta, dim3((unsigned)((rend - rbeg + 255) / 256)), dim3(256), 0,
-                           s->stream, s->d.dual_theta, rbeg, rend, (uint32_t)t, (uint32_t)s->rid0,
-                           (uint32_t)(s->seed & 0xffffffffu), (uint32_t)(s->seed >> 32), sc.window,
-                           (uint32_t)sc.tshift, sc.tscale);
-        if (int rc = checked("k_theta")) return rc;
-      }
+      bool twisted = false;
       const Entry *entries = static_cast<const Entry *>(s->d.dual_entries);
       for (int32_t q = 0; q < rounds; q++) {
-        if (!s->dual_pays[(size_t)q] && !(fused && q == rounds - 1)) {
+        const Entry *const here = entries;
+        entries += s->dual_count[(size_t)q];
+        const bool fused = twist_now && !s->has_h && q == rounds - 1;
+        if (!(s->dual_pays[(size_t)q] || fused) || drop) {
+          if (s->dual_pays[(size_t)q] || fused) drop = false;
           for (int32_t c = 2 * q; c < std::min(s->C, 2 * q + 2); c++)
             if (int rc = launch_class_hbm(s, c, alpha, rbeg, rend - rbeg)) return rc;
-          entries += s->dual_count[(size_t)q];
           continue;
         }
-        const float *theta = fused && q == rounds - 1 ? s->d.dual_theta : nullptr;
-        const float twist = host_twist(sc, t);
-        const int rc = vec == 4   ? pass<ST, 4>(s, q, entries, rbeg, rend, alpha, theta, twist)
-                       : vec == 2 ? pass<ST, 2>(s, q, entries, rbeg, rend, alpha, theta, twist)
-                                  : pass<ST, 1>(s, q, entries, rbeg, rend, alpha, theta, twist);
+        if (fused) {
+          hipLaunchKernelGGL(k_theta, dim3((unsigned)((rend - rbeg + 255) / 256)), dim3(256), 0,
+                             s->stream, s->d.dual_theta, rbeg, rend, (uint32_t)t,
+                             (uint32_t)s->rid0, (uint32_t)(s->seed & 0xffffffffu),
+                             (uint32_t)(s->seed >> 32), sc.window, (uint32_t)sc.tshift, sc.tscale);
+          if (int rc = checked("k_theta")) return rc;
+        }
+        const float *theta = fused ? s->d.dual_theta : nullptr;
+        const int rc = vec == 4   ? pass<ST, 4>(s, q, here, rbeg, rend, alpha, theta, twist)
+                       : vec == 2 ? pass<ST, 2>(s, q, here, rbeg, rend, alpha, theta, twist)
+                                  : pass<ST, 1>(s, q, here, rbeg, rend, alpha, theta, twist);
         if (rc) return rc;
-        entries += s->dual_count[(size_t)q];
+        twisted = fused;
         std::swap(s->d.phases, s->d.phases_alt);
       }
       if (s->has_h)
         if (int rc = launch_field_hbm(s, alpha, rbeg, rend - rbeg)) return rc;
-      if (twist_now && !fused)
+      if (twist_now && !twisted)
         if (int rc = launch_dwt_hbm(s, t, rbeg, rend - rbeg)) return rc;
     }
     rbeg = rend;
