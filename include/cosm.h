@@ -178,7 +178,11 @@ int cosm_build_partitions(int32_t n, int64_t m, const int32_t *eu, const int32_t
                           int32_t *num_colours_out);
 
 /* ---- state ------------------------------------------------------------------ */
-/* Device bytes cosm_init needs when the caller supplies the workspace. */
+/* Device bytes cosm_init needs when the caller supplies the workspace.  For graphs
+ * past the LDS (residency AUTO or HBM) this includes a second phase buffer and
+ * tables for sweeps of two colour classes per launch; a workspace without room for
+ * these is taken too (the bytes with residency PLAIN are the least) and gives the
+ * same results in more time. */
 int cosm_workspace_bytes(int32_t n, int64_t m, int32_t num_colours, int32_t replicas,
                          const cosm_params *p, size_t *bytes_out);
 
@@ -198,8 +202,8 @@ int cosm_workspace_bytes(int32_t n, int64_t m, int32_t num_colours, int32_t repl
  *     colouring; classes are applied in index order.
  *   hip_stream: a hipStream_t or NULL for the default stream.
  *   device_workspace / workspace_bytes: device memory the state uses for all its
- *     buffers (at least cosm_workspace_bytes), owned by the caller, kept alive
- *     until cosm_destroy; NULL makes the library allocate its own.
+ *     buffers (cosm_workspace_bytes), owned by the caller, kept alive until
+ *     cosm_destroy; NULL makes the library allocate its own.
  * Errors: EINVAL, EDUP, ECOLOR (not a proper colouring), ERANGE (alpha0*|J|,
  * dwt_ratio*alpha0 or the window not below a full turn; GRID with 2*dwt_ratio
  * not an integer or a window off the 2^-23 turn grid; forced LDS residency that
@@ -221,8 +225,8 @@ int cosm_init(cosm_state **out, int32_t n, int64_t m, const int32_t *eu, const i
  * second cosm_init_static on the same device fails with ESTATE until the first
  * state is cosm_destroy'ed; states made this way on different devices are
  * independent.  The array keeps whatever the last state left in it; every
- * buffer is written before it is read.  Errors: those of cosm_init, ERANGE when
- * cosm_workspace_bytes exceeds 32 MiB, ESTATE as above.  Later calls on the
+ * buffer is written before it is read.  Errors: those of cosm_init, ERANGE when the
+ * least workspace (cosm_workspace_bytes) exceeds 32 MiB, ESTATE as above.  Later calls on the
  * state behave as for cosm_init (cosm_get_phases / cosm_set_phases still
  * allocate a staging buffer; cosm_set_timing creates its events). */
 int cosm_init_static(cosm_state **out, int32_t n, int64_t m, const int32_t *eu, const int32_t *ev,

@@ -279,11 +279,22 @@ class State:
             self._h_state = handle
             return
         if torch_workspace:
-            nbytes = ctypes.c_size_t(0)
-            _check(L.cosm_workspace_bytes(self.n, self.m, int(num_colours), self.R,
-                                          ctypes.byref(cp), ctypes.byref(nbytes)))
-            self._ws = torch.empty(int(nbytes.value), dtype=torch.uint8, device="cuda")
-            ws_ptr, ws_bytes = ctypes.c_void_p(self._ws.data_ptr()), int(nbytes.value)
+            def needed(cp):
+                nbytes = ctypes.c_size_t(0)
+                _check(L.cosm_workspace_bytes(self.n, self.m, int(num_colours), self.R,
+                                              ctypes.byref(cp), ctypes.byref(nbytes)))
+                return int(nbytes.value)
+            ws_bytes = needed(cp)
+            try:
+                self._ws = torch.empty(ws_bytes, dtype=torch.uint8, device="cuda")
+            except torch.cuda.OutOfMemoryError:
+                least = self.params._c()  # without the buffers that only save time
+                least.residency = RES_PLAIN
+                if needed(least) >= ws_bytes:
+                    raise
+                ws_bytes = needed(least)
+                self._ws = torch.empty(ws_bytes, dtype=torch.uint8, device="cuda")
+            ws_ptr = ctypes.c_void_p(self._ws.data_ptr())
         handle = ctypes.c_void_p()
         _check(L.cosm_init(ctypes.byref(handle), self.n, self.m, _ptr(self._eu), _ptr(self._ev),
                            _ptr(self._J), _ptr(self._h), _ptr(self._colour), int(num_colours),

@@ -34,8 +34,21 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 struct MemPlan {
   size_t phases, desc, jmag, class_off, slot_vertex, reg_vertex, rs_words, rs_pwords, rs_act, h_slot, eu, ev, J, h, peu, pev, pJ, spins, H, cut, best_p,
       inc_off, inc_nbr, inc_J, phases_alt, opt_keys, opt_keys2, opt_vals, opt_vals2, opt_off,
-      opt_temp, opt_temp_bytes, codes, dual_entries, dual_theta, total;
+      opt_temp, opt_temp_bytes, codes, total;
 };
+// The buffers of the two-class device-memory sweeps, after all others.
+struct DualPlan {
+  size_t phases_alt, entries, theta, total;
+};
+
+DualPlan plan_dual(size_t before, int32_t n, int32_t R, const cosm_params &p, size_t entry_bytes) {
+  DualPlan dp{};
+  dp.phases_alt = before;
+  dp.entries = align_up(dp.phases_alt + (size_t)n * (size_t)R * storage_bytes(p.storage), 256);
+  dp.theta = align_up(dp.entries + entry_bytes, 256);
+  dp.total = align_up(dp.theta + (size_t)R * 4, 256);
+  return dp;
+}
 
 MemPlan plan_memory(int32_t n, int64_t m, int32_t C, int32_t R, const cosm_params &p) {
   MemPlan mp{};
@@ -79,10 +92,7 @@ MemPlan plan_memory(int32_t n, int64_t m, int32_t C, int32_t R, const cosm_param
   mp.inc_off = take(fg ? ((size_t)n + 1) * 4 : 0);
   mp.inc_nbr = take(fg ? (size_t)(2 * m) * 4 : 0);
   mp.inc_J = take(fg ? (size_t)(2 * m) * 4 : 0);
-  const bool dual = dual_hbm_form(n, m, C, R, p);
-  mp.phases_alt = take(fg || dual ? nr * storage_bytes(p.storage) : 0);
-  mp.dual_entries = take(dual ? dual_hbm_entry_bytes(n, m, C) : 0);
-  mp.dual_theta = take(dual ? (size_t)R * 4 : 0);
+  mp.phases_alt = take(fg ? nr * storage_bytes(p.storage) : 0);
   const bool opt = p.readout == COSM_READOUT_OPTIMAL;
   mp.opt_keys = take(opt ? nr * 4 : 0);
   mp.opt_keys2 = take(opt ? nr * 4 : 0);
@@ -384,7 +394,9 @@ int cosm_workspace_bytes(int32_t n, int64_t m, int32_t num_colours, int32_t repl
   if (int rc = check_params(p)) return rc;
   if (n < 1 || m < 0 || num_colours < 0 || replicas < 1)
     return set_error(COSM_EINVAL, "bad sizes");
-  *bytes_out = plan_memory(n, m, num_colours, replicas, *p).total;
+  *bytes_out = least_workspace_bytes(n, m, num_colours, replicas, *p);
+  if (dual_hbm_form(n, m, num_colours, replicas, *p))
+    *bytes_out = plan_dual(*bytes_out, n, replicas, *p, dual_hbm_entry_bytes(n, m, num_colours)).total;
   return COSM_OK;
 }
 
@@ -400,6 +412,10 @@ int cosm_init(cosm_state **out, int32_t n, int64_t m, const int32_t *eu, const i
 }  // extern "C"
 
 namespace cosm {
+
+size_t least_workspace_bytes(int32_t n, int64_t m, int32_t C, int32_t R, const cosm_params &p) {
+  return plan_memory(n, m, C, R, p).total;
+}
 
 int init_state(cosm_state **out, int32_t n, int64_t m, const int32_t *eu, const int32_t *ev,
                const int32_t *J, const int32_t *h, const int32_t *colour, int32_t num_colours,
@@ -536,22 +552,34 @@ int init_state(cosm_state **out, int32_t n, int64_t m, const int32_t *eu, const 
                         !(tune_env && tune_env[0] == '0');
 
   const MemPlan mp = plan_memory(n, m, num_colours, replicas, s->p);
+  // (the two-class device-memory sweeps where there is room for their buffers)
+  const size_t dual_bytes = s->shape.residency == COSM_RES_HBM &&
+                                    dual_hbm_form(n, m, num_colours, replicas, s->p)
+                                ? dual_hbm_choose(s) : 0;
+  const DualPlan dp = plan_dual(mp.total, n, replicas, s->p, dual_bytes);
+  bool dual = dual_bytes > 0;
   if (device_workspace != nullptr) {
     if (workspace_bytes < mp.total) {
       delete s;
       return set_error(COSM_ENOMEM, "workspace smaller than cosm_workspace_bytes()");
     }
+    dual = dual && workspace_bytes >= dp.total;
     s->base = device_workspace;
     s->own_memory = false;
   } else {
-    if (hipMalloc(&s->base, mp.total) != hipSuccess) {
+    if (dual && hipMalloc(&s->base, dp.total) != hipSuccess) {
+      (void)hipGetLastError();
+      dual = false;
+    }
+    if (!dual && hipMalloc(&s->base, mp.total) != hipSuccess) {
       (void)hipGetLastError();
       delete s;
       return set_error(COSM_ENOMEM, "hipMalloc of the state's buffers failed");
     }
     s->own_memory = true;
   }
-  s->base_bytes = mp.total;
+  if (!dual) s->dual_pays.clear();
+  s->base_bytes = dual ? dp.total : mp.total;
   DeviceBuffers &d = s->d;
   d.phases = at<void>(s->base, mp.phases);
   d.desc = at<EdgeDesc>(s->base, mp.desc);
@@ -577,9 +605,11 @@ int init_state(cosm_state **out, int32_t n, int64_t m, const int32_t *eu, const 
   d.inc_off = at<int32_t>(s->base, mp.inc_off);
   d.inc_nbr = at<uint32_t>(s->base, mp.inc_nbr);
   d.inc_J = at<float>(s->base, mp.inc_J);
-  d.phases_alt = at<void>(s->base, mp.phases_alt);
-  d.dual_entries = at<void>(s->base, mp.dual_entries);
-  d.dual_theta = at<float>(s->base, mp.dual_theta);
+  d.phases_alt = at<void>(s->base, dual ? dp.phases_alt : mp.phases_alt);
+  if (dual) {
+    d.dual_entries = at<void>(s->base, dp.entries);
+    d.dual_theta = at<float>(s->base, dp.theta);
+  }
   d.opt_keys = at<uint32_t>(s->base, mp.opt_keys);
   d.opt_keys2 = at<uint32_t>(s->base, mp.opt_keys2);
   d.opt_vals = at<uint32_t>(s->base, mp.opt_vals);
@@ -604,8 +634,7 @@ int init_state(cosm_state **out, int32_t n, int64_t m, const int32_t *eu, const 
   rc = rc ? rc : up(d.peu, peu.data(), (size_t)m * 4);
   rc = rc ? rc : up(d.pev, pev.data(), (size_t)m * 4);
   rc = rc ? rc : up(d.pJ, pJ.data(), (size_t)m * 4);
-  if (s->shape.residency == COSM_RES_HBM && dual_hbm_form(n, m, num_colours, replicas, s->p))
-    rc = rc ? rc : upload_dual_hbm(s);
+  if (dual) rc = rc ? rc : upload_dual_hbm(s);
   if (s->p.update == COSM_UPDATE_FULL_GRADIENT) {
     rc = rc ? rc : up(d.inc_off, inc_off.data(), inc_off.size() * 4);
     rc = rc ? rc : up(d.inc_nbr, inc_nbr.data(), inc_nbr.size() * 4);

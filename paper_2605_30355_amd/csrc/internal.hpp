@@ -305,6 +305,9 @@ int init_state(cosm_state **out, int32_t n, int64_t m, const int32_t *eu, const 
                const int32_t *J, const int32_t *h, const int32_t *colour, int32_t num_colours,
                const cosm_params *p, uint64_t seed, int32_t replicas, void *hip_stream,
                void *device_workspace, size_t workspace_bytes, int32_t static_dev);
+// What it needs at least: cosm_workspace_bytes without the buffers that only make the
+// sweeps of a graph past the LDS faster.
+size_t least_workspace_bytes(int32_t n, int64_t m, int32_t C, int32_t R, const cosm_params &p);
 // Releases the static scratch array of a device held by a state (static_scratch.hip).
 void release_static_scratch(int32_t dev);
 
@@ -404,10 +407,12 @@ struct DualEntry {
 std::vector<std::vector<DualEntry>> dual_entries(const cosm_state &s,
                                                  const std::vector<uint8_t> *wanted = nullptr);
 // The device-memory sweeps two classes at a time (sweep_dual_hbm.hip): whether a
-// state of these sizes may take them (it then has a second phase buffer and the
-// entries in device memory), and its launcher.
+// state of these sizes may take them, with a second phase buffer and the entries in
+// device memory (their bytes at most; those of the rounds chosen, 0 where no round
+// pays), and its launcher.
 bool dual_hbm_form(int32_t n, int64_t m, int32_t C, int32_t R, const cosm_params &p);
 size_t dual_hbm_entry_bytes(int32_t n, int64_t m, int32_t C);
+size_t dual_hbm_choose(cosm_state *s);
 int upload_dual_hbm(cosm_state *s);
 int launch_sweeps_dual_hbm(cosm_state *s, int64_t n_sweeps);
 // Two-class form (sweep_dual.hip; small graphs): its schedule for rows of W

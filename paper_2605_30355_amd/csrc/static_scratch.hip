@@ -47,6 +47,7 @@ extern "C" int cosm_init_static(cosm_state **out, int32_t n, int64_t m, const in
   *out = nullptr;
   size_t need = 0;
   if (int rc = cosm_workspace_bytes(n, m, num_colours, replicas, p, &need)) return rc;
+  need = least_workspace_bytes(n, m, num_colours, replicas, *p);
   if (need > kStaticScratchBytes)
     return set_error(COSM_ERANGE, "the state needs " + std::to_string(need) +
                                       " bytes of device memory; the static scratch array holds " +

@@ -38,7 +38,8 @@ namespace {
 constexpr size_t kGroupBytes = (size_t)192 << 20;
 // The second buffer is taken up to this size of the first.
 constexpr size_t kAltBytesMax = (size_t)16 << 30;
-// Vertices from which no replica fits in LDS.
+// Smaller graphs forced into device memory take a pass per class: the baseline that the
+// LDS forms are compared with.
 constexpr int32_t kVerticesMin = 40001;
 
 struct Entry {
@@ -241,10 +242,14 @@ int sweeps(cosm_state *s, int64_t n_sweeps) {
 }  // namespace
 
 bool dual_hbm_form(int32_t n, int64_t m, int32_t C, int32_t R, const cosm_params &p) {
-  const size_t elem = p.storage == COSM_STORE_FP32 || p.storage == COSM_STORE_FIX32 ? 4 : 2;
-  return n >= kVerticesMin && dual_hbm_entry_bytes(n, m, C) > 0 && p.update == COSM_UPDATE_SCS &&
-         (p.residency == COSM_RES_AUTO || p.residency == COSM_RES_HBM) &&
-         (size_t)n * (size_t)R * elem <= kAltBytesMax;
+  const int32_t pw = p.storage == COSM_STORE_FP32 || p.storage == COSM_STORE_FIX32 ? 1 : 2;
+  if (n < kVerticesMin || dual_hbm_entry_bytes(n, m, C) == 0 || p.update != COSM_UPDATE_SCS ||
+      (size_t)n * (size_t)R * (size_t)(4 / pw) > kAltBytesMax)
+    return false;
+  if (p.residency != COSM_RES_AUTO) return p.residency == COSM_RES_HBM;
+  // (one word per row fits up to some 40370 vertices: those run in LDS)
+  return n > 65535 || lds_sweep_bytes(n, std::max(1, p.replicas_per_wg / pw), C) >
+                          (size_t)lds_capacity_bytes();
 }
 
 size_t dual_hbm_entry_bytes(int32_t n, int64_t m, int32_t C) {
@@ -256,25 +261,29 @@ size_t dual_hbm_entry_bytes(int32_t n, int64_t m, int32_t C) {
   return (size_t)std::min<int64_t>((C + 1) / 2, pay + 1) * ((size_t)n / 2 + 1) * sizeof(Entry);
 }
 
-int upload_dual_hbm(cosm_state *s) {
+size_t dual_hbm_choose(cosm_state *s) {
   std::vector<uint8_t> pays((size_t)(s->C + 1) / 2, 0);
-  bool any = false;
+  size_t rounds = 0;
   for (int32_t q = 0; 2 * q + 1 < s->C; q++) {
     pays[(size_t)q] = round_pays(s->n, s->class_sizes[(size_t)2 * q], s->class_sizes[(size_t)2 * q + 1]);
-    any = any || pays[(size_t)q];
+    rounds += pays[(size_t)q];
   }
-  if (!any) return COSM_OK;
+  if (rounds == 0) return 0;
+  if (!pays.back() && s->sched.dwt_period > 0 && !s->has_h) rounds++;  // (the twist's)
   s->dual_pays = pays;
-  if (s->sched.dwt_period > 0 && !s->has_h) pays.back() = 1;
+  return rounds * ((size_t)s->n / 2 + 1) * sizeof(Entry);
+}
+
+int upload_dual_hbm(cosm_state *s) {
+  std::vector<uint8_t> wanted(s->dual_pays);
+  if (s->sched.dwt_period > 0 && !s->has_h) wanted.back() = 1;
   std::vector<Entry> all;
-  for (const auto &round : dual_entries(*s, &pays)) {
+  for (const auto &round : dual_entries(*s, &wanted)) {
     s->dual_count.push_back((int32_t)round.size());
     for (const DualEntry &e : round)
       all.push_back(Entry{e.u, e.v, e.pu, e.pv, (float)e.J, (float)e.Ju, (float)e.Jv,
                           e.fu | e.fv << 1});
   }
-  if (all.size() * sizeof(Entry) > dual_hbm_entry_bytes(s->n, s->m, s->C))
-    return set_error(COSM_ERANGE, "internal error: entries past their buffer");
   COSM_HIP_CHECK(hipMemcpyAsync(s->d.dual_entries, all.data(), all.size() * sizeof(Entry),
                                 hipMemcpyHostToDevice, s->stream));
   COSM_HIP_CHECK(hipStreamSynchronize(s->stream));  // all goes out of scope
