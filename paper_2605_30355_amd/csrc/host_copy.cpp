@@ -54,9 +54,19 @@ std::mutex g_mu;
 Block *g_pool[kPoolMax];
 int g_count = 0;
 
-Block *take_block() {
+// A block of the current device, or null: out of memory, or the stream is another
+// device's (whose events would have to be made with that device current).
+Block *take_block(hipStream_t stream) {
   int dev = 0;
+  hipDevice_t own = 0;
   if (hipGetDevice(&dev) != hipSuccess) return nullptr;
+  if (stream != nullptr) {
+    if (hipStreamGetDevice(stream, &own) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    if (own != dev) return nullptr;
+  }
   {
     std::lock_guard<std::mutex> lk(g_mu);
     for (int i = 0; i < g_count; i++)
@@ -173,7 +183,7 @@ int plain(hipStream_t stream, const HostPiece *p, int count) {
 }  // namespace
 
 int copy_to_host(hipStream_t stream, HostPiece *p, int count, bool may_allocate) {
-  Block *b = may_allocate ? take_block() : nullptr;
+  Block *b = may_allocate ? take_block(stream) : nullptr;
   if (b == nullptr) return plain(stream, p, count);
   std::sort(p, p + count, [](const HostPiece &x, const HostPiece &y) { return x.src < y.src; });
   // the short pieces: neighbours in one copy, waited for with the long ones' or last

@@ -21,8 +21,8 @@ def checker(tmp_path_factory):
     return out
 
 
-def run(checker, lengths):
-    r = subprocess.run([checker, *map(str, lengths)], capture_output=True, text=True, timeout=120)
+def run(checker, lengths, device=0):
+    r = subprocess.run([checker, str(device), *map(str, lengths)], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stderr
     got = [dict(kv.split("=") for kv in line.split()) for line in r.stdout.splitlines()]
     assert [int(g["len"]) for g in got] == list(lengths)
@@ -40,3 +40,8 @@ def test_lengths_around_every_share(checker):
     # 753 x 3601, 1003 x 3267 and 271 x 271 x 999 spins
     lengths += [753 * 3601, 1003 * 3267, 271 * 271 * 999]
     assert run(checker, lengths) == []
+
+
+def test_stream_of_another_device(checker):
+    """Results of a batch may be asked for with another device current than its own."""
+    assert run(checker, [800, 200000, 3 << 20, 20 << 20], device=1) == []
