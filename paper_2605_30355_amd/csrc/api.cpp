@@ -684,6 +684,7 @@ int cosm_reset(cosm_state *s, uint64_t seed, int64_t replica_offset) {
   s->rid0 = replica_offset;
   s->t = 0;
   s->on_grid = true;
+  return_to_dual_shape(s);
   return launch_init(s);
 }
 
@@ -832,6 +833,10 @@ int cosm_set_phases(cosm_state *s, int32_t unit, const double *in, int64_t t) {
       const float q = f * 8388608.0f;  // exact: a scaling by 2^23
       on_grid = on_grid && q == std::floor(q);
     }
+  // the two-class form decides an edge's sign once at either end, which agrees for
+  // differences that are exact: on the grid
+  if (!on_grid && s->p.storage == COSM_STORE_FP32)
+    if (int rc = leave_dual_shape(s)) return rc;
   float *tmp = nullptr;
   COSM_HIP_CHECK(hipMalloc(&tmp, nr * 4));
   int rc = COSM_OK;
@@ -843,9 +848,7 @@ int cosm_set_phases(cosm_state *s, int32_t unit, const double *in, int64_t t) {
   if (!rc) {
     s->t = t;
     s->on_grid = on_grid;
-    // the two-class form decides an edge's sign once at either end, which agrees
-    // for differences that are exact: on the grid
-    if (!on_grid && s->lds.dual && s->p.storage == COSM_STORE_FP32) rc = use_pair_shape(s);
+    if (on_grid) return_to_dual_shape(s);
   }
   return rc;
 }

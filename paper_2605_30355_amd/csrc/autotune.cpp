@@ -88,9 +88,29 @@ int apply_shape(cosm_state *s, int32_t W, int32_t nth, int32_t pw, int32_t K,
 
 }  // namespace
 
-int use_pair_shape(cosm_state *s) {
-  const int32_t pw = (s->p.storage == COSM_STORE_FP32 || s->p.storage == COSM_STORE_FIX32) ? 1 : 2;
-  return apply_shape(s, s->shape.rw / pw, 0, pw, 0);
+int leave_dual_shape(cosm_state *s) {
+  if (!s->lds.dual) return COSM_OK;
+  if (s->away_lds.slot_vertex.empty()) {
+    // the pair layout's tables beside the two-class form's (which stay on the device)
+    s->away_lds = s->lds;
+    s->away_shape = s->shape;
+    if (int rc = apply_shape(s, s->shape.rw, s->p.threads_per_wg, 1, 0)) {
+      s->lds = std::move(s->away_lds);
+      s->shape = s->away_shape;
+      s->away_lds = LdsSchedule();
+      return rc;
+    }
+  } else {
+    std::swap(s->lds, s->away_lds);
+    std::swap(s->shape, s->away_shape);
+  }
+  return COSM_OK;
+}
+
+void return_to_dual_shape(cosm_state *s) {
+  if (!s->away_lds.dual) return;
+  std::swap(s->lds, s->away_lds);
+  std::swap(s->shape, s->away_shape);
 }
 
 int upload_lds_schedule(cosm_state *s) {
@@ -116,7 +136,8 @@ int upload_lds_schedule(cosm_state *s) {
       COSM_HIP_CHECK(hipMemcpyAsync(s->d.reg_vertex, L.K.data(), L.K.size() * 4,
                                     hipMemcpyHostToDevice, s->stream));
     if (int rc = upload_h_slot(s)) return rc;
-    COSM_HIP_CHECK(hipMemcpyAsync(s->d.slot_vertex, L.slot_vertex.data(),
+    // (the two-class form's slot map keeps out of the pair layout's place)
+    COSM_HIP_CHECK(hipMemcpyAsync(L.dual ? s->d.reg_vertex : s->d.slot_vertex, L.slot_vertex.data(),
                                   L.slot_vertex.size() * 4, hipMemcpyHostToDevice, s->stream));
     COSM_HIP_CHECK(hipStreamSynchronize(s->stream));  // host vectors may change next
     return COSM_OK;

@@ -268,6 +268,10 @@ struct cosm_state {
   int32_t cus = 256;  // compute units of the device
   mutable std::vector<uint8_t> indep;  // independent set of the register forms, once found
   cosm::LdsSchedule lds;  // resolved lane schedule of the LDS form
+  // the schedule and shape not in use, once FP32 phases have left the grid in the
+  // two-class form: the pair layout's or, while they are off it, the two-class form's
+  cosm::LdsSchedule away_lds;
+  cosm::KernelShape away_shape;
   std::vector<int32_t> lds_widths;  // row widths (words) that fit, for the autotuner
   bool has_h = false;
   int64_t sumJ = 0;                 // sum of J over the edges
@@ -461,9 +465,11 @@ int pick_reg_schedule(cosm_state *s, int32_t W, int32_t nth);
 int rstream_schedule_for(const cosm_state &s, int32_t W, int32_t nth, LdsSchedule *out);
 // Measure candidate LDS shapes (row widths in words) and keep the fastest.
 int autotune_lds_shape(cosm_state *s, const std::vector<int32_t> &widths);
-// Puts the state into the pair layout at its row width (for FP32 phases off the
-// grid, which the two-class form's one-sided updates need).
-int use_pair_shape(cosm_state *s);
+// From the two-class form into the pair layout at its row width, for FP32 phases off the
+// grid (the one-sided updates need exact differences), and back (host only) for phases on
+// it; nothing for a state in another form.
+int leave_dual_shape(cosm_state *s);
+void return_to_dual_shape(cosm_state *s);
 // Uploads the bias field in LDS-slot order (no-op without bias fields).
 int upload_h_slot(cosm_state *s);
 // Uploads s->lds (the schedule in the kernel's encoding, the slots per class,

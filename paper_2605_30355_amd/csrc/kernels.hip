@@ -555,7 +555,7 @@ int sweeps_lds_st(cosm_state *s, int64_t n_sweeps) {
   a.phases = s->d.phases;
   a.desc = s->d.desc;
   a.Kc = s->d.class_off;
-  a.slot_vertex = s->d.slot_vertex;
+  a.slot_vertex = s->lds.dual ? s->d.reg_vertex : s->d.slot_vertex;
   a.h_slot = s->has_h ? s->d.h_slot : nullptr;
   a.R = s->R;
   a.n_rows = s->lds.n_rows;
