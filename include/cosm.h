@@ -303,7 +303,8 @@ int cosm_batch_destroy(cosm_batch *b);
  * short probe runs of one full work item of the instance (as many replica
  * sets as fit one workgroup, up to 128 sweeps; the stream is synchronised;
  * results are cached per process by the instance's sizes, storage, replicas,
- * sweeps and a hash of its edges and colouring). */
+ * sweeps, the kernel path its couplings and schedule select, and a hash of its
+ * edges and colouring). */
 int cosm_batch_add_graph(cosm_batch *b, int32_t n, int64_t m, const int32_t *eu,
                          const int32_t *ev, const int32_t *J, const int32_t *colour,
                          int32_t num_colours, const cosm_params *p, uint64_t seed,

@@ -689,8 +689,8 @@ int launch_run(cosm_batch *b) {
 // width with the least is kept.  (Timing the graph alone with all its
 // replicas would instead favour the narrow rows that spread a lone graph over
 // more CUs.)  The choice is cached by the instance's signature (sizes,
-// storage, replicas, sweeps and an FNV-1a hash of the edge list and
-// colouring), so later graphs with the same signature skip the probes.  The
+// storage, replicas, sweeps, the kernel path and an FNV-1a hash of the edge list
+// and colouring), so later graphs with the same signature skip the probes.  The
 // probe overwrites only the graph's own first replicas' phases and results,
 // which every run initialises afresh.
 std::mutex g_tune_mu;
@@ -709,7 +709,12 @@ int tune_batch_graph(cosm_batch *b, BatchGraphHost *g, const std::vector<int32_t
     mix((uint32_t)s.h_ev[(size_t)k]);
     mix((uint32_t)s.h_colour[(size_t)k]);
   }
-  const std::vector<int64_t> key{s.n, s.m, s.C, s.R, b->storage, s.p.sweeps_per_trial, (int64_t)h};
+  // the kernel path too: the word schedule at each width, the FP32 sweep variant, the
+  // 16-bit wrap
+  int64_t path = !s.sched.grid ? 0 : wrap_at_twists(s) ? 2 : 1;
+  path = path * 2 + (lazy16(s) ? 1 : 0);
+  for (int32_t w : {4, 2, 1}) path = path * 2 + (batch_words_apply(s, s.C, w, b->lds_budget) ? 1 : 0);
+  const std::vector<int64_t> key{s.n, s.m, s.C, s.R, b->storage, s.p.sweeps_per_trial, path, (int64_t)h};
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tune_cache.find(key);
