@@ -664,6 +664,14 @@ int sweeps_hbm_st(cosm_state *s, int64_t n_sweeps) {
     if (sc.dwt_period > 0 && t % sc.dwt_period == 0)
       if (int rc = dwt_hbm_st<ST>(s, t, 0, s->R)) return rc;
   }
+  // (a call leaves the phases in the buffer it found them in: one that is captured into
+  // a graph keeps its buffers, whatever calls run between the graph's replays)
+  if (s->p.update == COSM_UPDATE_FULL_GRADIENT && n_sweeps % 2 != 0) {
+    std::swap(s->d.phases, s->d.phases_alt);
+    COSM_HIP_CHECK(hipMemcpyAsync(s->d.phases, s->d.phases_alt,
+                                  (size_t)s->n * s->R * (4 / Fmt<ST>::kPerWord),
+                                  hipMemcpyDeviceToDevice, s->stream));
+  }
   return COSM_OK;
 }
 
