@@ -83,7 +83,8 @@ enum { COSM_STORE_FP32 = 0, COSM_STORE_FP16 = 1, COSM_STORE_BF16 = 2, COSM_STORE
  * one launch per colour class (two per launch on graphs past the LDS, which then
  * need a second phase buffer).  PLAIN: one replica per launch, one launch per
  * colour class (the unbatched baseline).  AUTO: LDS where a replica fits (with
- * FULL_GRADIENT where two copies of it do), else HBM. */
+ * FULL_GRADIENT where two copies of it do, and the replicas keep enough CUs busy),
+ * else HBM. */
 enum { COSM_RES_AUTO = 0, COSM_RES_LDS = 1, COSM_RES_HBM = 2, COSM_RES_PLAIN = 3 };
 /* GRID: every phase, step and angle is a multiple of 2^-23 turn (2^-16 with
  * FIX16 storage), so sweeps are exact; the window must be a multiple of 2^-22

@@ -210,10 +210,26 @@ size_t full_lds_bytes(int32_t n, int W) {
          (size_t)((n + 63) / 64) * 4;
 }
 
+// With few replicas most CUs are idle in LDS, and a sweep takes its one workgroup as
+// long as it has vertices and neighbours to visit; in device memory all CUs share them,
+// and a sweep waits for launches, its longest vertex and, on twist sweeps, the twist's
+// strips.  Both in us a sweep, fitted on 3-regular and Erdos-Renyi graphs of 4000 - 19000
+// vertices, 1 - 128 replicas, within some 15 %.  LDS | device memory, period 6: FP32,
+// 12000 vertices, 1 replica 7.4 | 5.2, 4 replicas 7.5 | 8.6; 19000 vertices, 16 replicas
+// 12.0 | 10.6, 64 12.1 | 16.8; FIX16, 19000, 32 replicas 17.7 | 13.9, 128 17.8 | 21.3.
+bool device_memory_faster(const cosm_state &s, int32_t dmax, bool wide) {
+  const double lds = (wide ? 0.155e-3 : 0.224e-3) * ((double)s.n + 2.0 * (double)s.m);
+  const double twist = s.R == 1 ? (wide ? 12 : 14) : s.R == 2 ? (wide ? 20 : 22) : (wide ? 32 : 41);
+  const double hbm = 2.2 + 0.35 * dmax + 7.5e-6 * (double)s.n * (double)s.R +
+                     (s.sched.dwt_period > 0 ? twist / s.sched.dwt_period : 0.0);
+  return hbm < lds;
+}
+
 }  // namespace
 
 // The rows of the LDS form, or COSM_ERANGE where it does not apply: two copies of
-// at least one word per vertex, |J| below 2^14, at most kFullDegreeMax neighbours.
+// at least one word per vertex, |J| below 2^14, at most kFullDegreeMax neighbours,
+// replicas enough (device_memory_faster).
 // Of the row widths that give every CU a workgroup the widest: a neighbour word and
 // its decoding serve all replicas of a row (2000 vertices, 2048 replicas: 1, 2 and
 // 4 words 1.82, 1.14 and 0.68 ms per 200 sweeps).
@@ -245,6 +261,8 @@ int full_shape(const cosm_state &s, int32_t cus, LdsSchedule *out, KernelShape *
   const int32_t dmax = degree[(size_t)L.slot_vertex[0]];
   if (dmax > kFullDegreeMax)
     return set_error(COSM_ERANGE, "full gradient: the LDS form takes 32 neighbours");
+  if (device_memory_faster(s, dmax, pw == 1))
+    return set_error(COSM_ERANGE, "full gradient: few replicas of a large graph");
   std::vector<int32_t> row((size_t)n);
   for (int32_t r = 0; r < n; r++) row[(size_t)L.slot_vertex[(size_t)r]] = r;
   // a padding word: the vertex itself with J = 0
