@@ -495,7 +495,6 @@ int init_state(cosm_state **out, int32_t n, int64_t m, const int32_t *eu, const 
   }
   if (h) s->h_h.assign(h, h + n);
   s->h_colour.assign(colour, colour + m);
-  find_wrap_bounds(s);
 
   // group the edges by class (stable): the plain / HBM arrays and LDS descriptors
   s->class_sizes.assign((size_t)num_colours, 0);
@@ -546,6 +545,7 @@ int init_state(cosm_state **out, int32_t n, int64_t m, const int32_t *eu, const 
     delete s;
     return rc;
   }
+  if (s->shape.residency == COSM_RES_LDS) find_wrap_bounds(s);
   const char *tune_env = std::getenv("COSM_AUTOTUNE");
   const bool autotune = static_dev < 0 && s->shape.residency == COSM_RES_LDS && p->replicas_per_wg == 0 &&
                         p->threads_per_wg == 0 && s->lds_widths.size() > 0 &&

@@ -360,7 +360,8 @@ bool wrap_at_twists(const cosm_state &s);
 // The same for the forms that take an edge's difference from either of its ends
 // (dual: the two-class form, else the streamed register owners), which also need it
 // below two turns, and the two-class form's for a wrap at the end of every sweep;
-// find_wrap_bounds fills in the state's part of these, once it has its schedule.
+// find_wrap_bounds fills in the state's part of these (LDS forms), once it has its
+// classes, schedule and phases on the grid.
 bool either_end_at_twists(const cosm_state &s, bool dual);
 bool dual_wrap_at_sweeps(const cosm_state &s);
 void find_wrap_bounds(cosm_state *s);

@@ -61,48 +61,47 @@ bool wrap_at_sweeps(const cosm_state &s) { return exact_grid_fp32(s) && grid_dri
 // other sign.  So the forms that decide an edge's sign at either end (sweep_dual.hip,
 // the owners of sweep_rstream.hip) need the difference exact, that is below two
 // turns: two phases start in [0, 1 + twist) and part by the steps that both ends can
-// have made before that edge's own update.  The steps are counted edge by edge (the
-// even classes only where first is set: the two-class form takes no other edge's
-// difference from the v end), in units of the largest step.
+// have made before that edge's own update.  They are counted edge by edge, in units of
+// the largest step (the two-class form's in the even classes only: it takes no other
+// edge's difference from the v end).  Once per state: its schedule and couplings do not
+// change.
 // 20 x 20 torus at 14 degrees, period 3: 0.80 of the one turn there is; 141 x 141
 // torus 0.88.
-namespace {
-double steps_before(const cosm_state &s, int32_t sweeps, bool first) {
-  std::vector<int64_t> all((size_t)s.n, 0), done((size_t)s.n, 0);
-  auto weight = [&](int32_t k) { return std::llabs((int64_t)s.h_J[(size_t)k]); };
-  std::vector<std::vector<int32_t>> classes((size_t)s.C);
-  for (int64_t k = 0; k < s.m; k++) {
-    classes[(size_t)s.h_colour[(size_t)k]].push_back((int32_t)k);
-    all[(size_t)s.h_eu[(size_t)k]] += weight((int32_t)k);
-    all[(size_t)s.h_ev[(size_t)k]] += weight((int32_t)k);
-  }
-  double most = 0.0;
-  for (int32_t c = 0; c < s.C; c++) {
-    for (int32_t k : classes[(size_t)c]) {
-      const size_t u = (size_t)s.h_eu[(size_t)k], v = (size_t)s.h_ev[(size_t)k];
-      if (weight(k) > 0 && !(first && c % 2 != 0))
-        most = std::max(most, (double)(sweeps - 1) * (double)(all[u] + all[v]) +
-                              (double)(done[u] + done[v]));
-      done[u] += weight(k);
-      done[v] += weight(k);
-    }
-  }
-  return most;
-}
-bool either_end_exact(const cosm_state &s, int32_t sweeps, bool first) {
-  return twist_max_turns(s.sched) +
-             alpha_max_turns(s.sched) * steps_before(s, sweeps, first) <= 1.0;
-}
-}  // namespace
-
-// Found once (the schedule and the couplings of a state do not change).
 void find_wrap_bounds(cosm_state *s) {
   s->dual_twists = s->dual_sweeps = s->owner_twists = false;
-  if (!exact_grid_fp32(*s)) return;
-  s->dual_sweeps = either_end_exact(*s, 1, true);
-  if (s->sched.dwt_period < 1) return;
-  s->dual_twists = either_end_exact(*s, s->sched.dwt_period, true);
-  s->owner_twists = either_end_exact(*s, s->sched.dwt_period, false);
+  if (!wrap_at_sweeps(*s)) return;
+  // edges class by class
+  std::vector<int32_t> at(s->class_begin), order((size_t)s->m);
+  for (int64_t k = 0; k < s->m; k++)
+    order[(size_t)at[(size_t)s->h_colour[(size_t)k]]++] = (int32_t)k;
+  // a vertex's steps in a whole sweep, and in the classes so far
+  std::vector<int64_t> all((size_t)s->n, 0), done((size_t)s->n, 0);
+  for (int64_t k = 0; k < s->m; k++) {
+    const int64_t w = std::llabs((int64_t)s->h_J[(size_t)k]);
+    all[(size_t)s->h_eu[(size_t)k]] += w;
+    all[(size_t)s->h_ev[(size_t)k]] += w;
+  }
+  const double before = (double)(std::max(1, s->sched.dwt_period) - 1);
+  double dual = 0.0, owner = 0.0, sweep = 0.0;
+  for (int32_t k : order) {
+    const size_t u = (size_t)s->h_eu[(size_t)k], v = (size_t)s->h_ev[(size_t)k];
+    const int64_t w = std::llabs((int64_t)s->h_J[(size_t)k]);
+    if (w == 0) continue;
+    const double here = (double)(done[u] + done[v]), period = before * (double)(all[u] + all[v]);
+    owner = std::max(owner, period + here);
+    if (s->h_colour[(size_t)k] % 2 == 0) {
+      dual = std::max(dual, period + here);
+      sweep = std::max(sweep, here);
+    }
+    done[u] += w;
+    done[v] += w;
+  }
+  auto exact = [&](double steps) {
+    return twist_max_turns(s->sched) + alpha_max_turns(s->sched) * steps <= 1.0;
+  };
+  s->dual_sweeps = exact(sweep);
+  s->dual_twists = exact(dual);
+  s->owner_twists = exact(owner);
 }
 bool either_end_at_twists(const cosm_state &s, bool dual) {
   return wrap_at_twists(s) && (dual ? s.dual_twists : s.owner_twists);

@@ -35,6 +35,10 @@ int main(int argc, char **argv) {
   s.sched.tunit = 1.0f / 8388608.0f;
   s.sched.twist_num2 = (int)(2.0 * ratio + 0.5);
   s.sched.dwt_period = period;
+  std::vector<int32_t> sizes(C, 0);
+  for (int c : s.h_colour) sizes[c]++;
+  s.class_begin.assign(C, 0);
+  for (int c = 1; c < C; c++) s.class_begin[c] = s.class_begin[c - 1] + sizes[c - 1];
   cosm::find_wrap_bounds(&s);
   // edge by edge, by walking over the sweeps between two twists
   const long step = 2 * s.sched.a0_units, start = (1L << 23) - 1 + s.sched.twist_num2 * s.sched.a0_units;
