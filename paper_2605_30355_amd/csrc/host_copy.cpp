@@ -8,6 +8,7 @@
 // memory, the device filling one while several threads empty those before it.
 #include <algorithm>
 #include <atomic>
+#include <condition_variable>
 #include <cstring>
 #include <memory>
 #include <mutex>
@@ -102,8 +103,8 @@ void give_block(Block *b) {
 }
 
 // One long piece in chunks through the block, emptied by a thread per two megabytes
-// (two at least).
-int copy_long(hipStream_t stream, Block *b, char *dst, const char *src, size_t bytes) {
+// (two at least).  idle: nothing else was in the stream.
+int copy_long(hipStream_t stream, Block *b, char *dst, const char *src, size_t bytes, bool idle) {
   const size_t kChunk = bytes < ((size_t)8 << 20) ? kChunkMax / 4 : kChunkMax;
   const int threads = (int)std::min<size_t>(
       {(size_t)kThreadsMax, std::max<size_t>(2, bytes >> 21), (size_t)std::thread::hardware_concurrency() / 2});
@@ -122,9 +123,26 @@ int copy_long(hipStream_t stream, Block *b, char *dst, const char *src, size_t b
     if (at < l)
       std::memcpy(dst + c * kChunk + at, b->mem + (c % kChunks) * kChunk + at, std::min(p, l - at));
   };
+  // While the device has work left (sweeps may take seconds) the threads sleep until the
+  // first chunk is there; then they follow the chunks, some tens of us apart.
+  std::mutex mu;
+  std::condition_variable first;
+  bool go = idle;
+  auto start = [&] {
+    if (idle) return;
+    {
+      std::lock_guard<std::mutex> lk(mu);
+      go = true;
+    }
+    first.notify_all();
+  };
   std::vector<std::thread> workers;
   int of = 1;
   auto work = [&](int k, int of) {
+    if (!idle) {
+      std::unique_lock<std::mutex> lk(mu);
+      first.wait(lk, [&] { return go; });
+    }
     for (size_t c = 0; c < n; c++) {
       while (ready.load(std::memory_order_acquire) <= c) {
         if (stop.load(std::memory_order_relaxed)) return;
@@ -140,6 +158,7 @@ int copy_long(hipStream_t stream, Block *b, char *dst, const char *src, size_t b
     of = threads;
   } catch (...) {  // fewer threads than parts: none, and this one copies
     stop.store(true);
+    start();
     for (std::thread &w : workers) w.join();
     workers.clear();
     of = 1;
@@ -162,8 +181,12 @@ int copy_long(hipStream_t stream, Block *b, char *dst, const char *src, size_t b
     if (workers.empty()) part(arrived, 0, 1);
     arrived++;
     ready.store(arrived, std::memory_order_release);
+    if (arrived == 1) start();
   }
-  if (err != hipSuccess) stop.store(true);
+  if (err != hipSuccess) {
+    stop.store(true);
+    start();
+  }
   for (std::thread &w : workers) w.join();
   if (err != hipSuccess) {
     (void)hipStreamSynchronize(stream);  // no copy into the block is left
@@ -185,6 +208,8 @@ int plain(hipStream_t stream, const HostPiece *p, int count) {
 int copy_to_host(hipStream_t stream, HostPiece *p, int count, bool may_allocate) {
   Block *b = may_allocate ? take_block(stream) : nullptr;
   if (b == nullptr) return plain(stream, p, count);
+  const bool idle = hipStreamQuery(stream) == hipSuccess;
+  if (!idle) (void)hipGetLastError();  // (not ready is no error)
   std::sort(p, p + count, [](const HostPiece &x, const HostPiece &y) { return x.src < y.src; });
   // the short pieces: neighbours in one copy, waited for with the long ones' or last
   char *const shorts = b->mem + kChunkMax * kChunks;
@@ -212,7 +237,7 @@ int copy_to_host(hipStream_t stream, HostPiece *p, int count, bool may_allocate)
   }
   for (int i = 0; i < count && rc == COSM_OK; i++)
     if (p[i].bytes >= kLong)
-      rc = copy_long(stream, b, (char *)p[i].dst, (const char *)p[i].src, p[i].bytes);
+      rc = copy_long(stream, b, (char *)p[i].dst, (const char *)p[i].src, p[i].bytes, idle);
     else if (p[i].bytes > kShort &&
              hipMemcpyAsync(p[i].dst, p[i].src, p[i].bytes, hipMemcpyDeviceToHost, stream) !=
                  hipSuccess)

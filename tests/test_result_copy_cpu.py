@@ -21,12 +21,16 @@ def checker(tmp_path_factory):
     return out
 
 
-def run(checker, lengths, device=0):
-    r = subprocess.run([checker, str(device), *map(str, lengths)], capture_output=True, text=True, timeout=120)
+def lines(checker, lengths, device=0, busy_ms=0):
+    r = subprocess.run([checker, str(device), str(busy_ms), *map(str, lengths)], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stderr
     got = [dict(kv.split("=") for kv in line.split()) for line in r.stdout.splitlines()]
     assert [int(g["len"]) for g in got] == list(lengths)
-    return [int(g["len"]) for g in got if g["bad"] != "0"]
+    return got
+
+
+def run(checker, lengths, device=0):
+    return [int(g["len"]) for g in lines(checker, lengths, device) if g["bad"] != "0"]
 
 
 def test_lengths_around_every_share(checker):
@@ -45,3 +49,10 @@ def test_lengths_around_every_share(checker):
 def test_stream_of_another_device(checker):
     """Results of a batch may be asked for with another device current than its own."""
     assert run(checker, [800, 200000, 3 << 20, 20 << 20], device=1) == []
+
+
+def test_the_threads_sleep_while_the_device_works(checker):
+    """Results are asked for while sweeps still run; a long trial must not cost its time on
+    every copying thread."""
+    for g in lines(checker, [3 << 20, 20 << 20], busy_ms=400):
+        assert g["bad"] == "0" and float(g["cpu_ms"]) < 200.0, g
