@@ -51,6 +51,32 @@ __device__ __forceinline__ void neighbour(const float (&xi)[RW], const float (&x
   }
 }
 
+// The twist of a row.  FIX32: on the decoded value, as in the device-memory form
+// (k_dwt_hbm), since phases set from outside may lie off the grid, where FP32 rounds them
+// and the integer twist of TwistOps would not.
+template <int ST, int W>
+struct RowTwist : TwistOps<ST, W> {};
+template <int W>
+struct RowTwist<COSM_STORE_FIX32, W> {
+  float c[W], t[W], win2;
+  __device__ __forceinline__ void set(const float (&cth)[W], const float (&tws)[W], float w2) {
+#pragma unroll
+    for (int k = 0; k < W; k++) {
+      c[k] = cth[k];
+      t[k] = tws[k];
+    }
+    win2 = w2;
+  }
+  __device__ __forceinline__ void apply(uint32_t (&w)[W]) const {
+    using F = Fmt<COSM_STORE_FIX32>;
+    float x[W];
+    F::template unpack<W>(w, x);
+#pragma unroll
+    for (int k = 0; k < W; k++)
+      if (in_windows(x[k], c[k], win2)) w[k] = F::enc(F::wrap(x[k] + t[k]));
+  }
+};
+
 template <int ST, int W, bool RD>
 __global__ void __launch_bounds__(1024) k_full_lds(const LdsArgs a) {
   static_assert(!RD || ST == COSM_STORE_FP32, "the parity step is an FP32 grid form");
@@ -88,7 +114,7 @@ __global__ void __launch_bounds__(1024) k_full_lds(const LdsArgs a) {
     float alpha, twist;
     chunk.get(it & 63u, alpha, twist);
     const bool twist_now = chunk.twist_at(it & 63u);
-    TwistOps<ST, W> op;
+    RowTwist<ST, W> op;
     if (twist_now) {
       const int q = (int)(tw % (uint32_t)kThetaChunk);
       tw++;
