@@ -396,7 +396,8 @@ int cosm_workspace_bytes(int32_t n, int64_t m, int32_t num_colours, int32_t repl
     return set_error(COSM_EINVAL, "bad sizes");
   *bytes_out = least_workspace_bytes(n, m, num_colours, replicas, *p);
   if (dual_hbm_form(n, m, num_colours, replicas, *p))
-    *bytes_out = plan_dual(*bytes_out, n, replicas, *p, dual_hbm_entry_bytes(n, m, num_colours)).total;
+    *bytes_out = plan_dual(*bytes_out, n, replicas, *p,
+                           dual_hbm_entry_bytes(n, m, num_colours, replicas)).total;
   return COSM_OK;
 }
 

@@ -416,7 +416,7 @@ std::vector<std::vector<DualEntry>> dual_entries(const cosm_state &s,
 // device memory (their bytes at most; those of the rounds chosen, 0 where no round
 // pays), and its launcher.
 bool dual_hbm_form(int32_t n, int64_t m, int32_t C, int32_t R, const cosm_params &p);
-size_t dual_hbm_entry_bytes(int32_t n, int64_t m, int32_t C);
+size_t dual_hbm_entry_bytes(int32_t n, int64_t m, int32_t C, int32_t R);
 size_t dual_hbm_choose(cosm_state *s);
 int upload_dual_hbm(cosm_state *s);
 int launch_sweeps_dual_hbm(cosm_state *s, int64_t n_sweeps);

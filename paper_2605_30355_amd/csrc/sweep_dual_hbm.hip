@@ -141,12 +141,15 @@ int checked(const char *what) {
 
 // Whether classes of a and b edges are worth a pass: it reads and writes n rows, and
 // reads the 2a partners' (from the caches); one class after the other reads and
-// writes 2(a + b).
-// Two such rounds on 60000 vertices, random partners, 1024 replicas, classes -> passes
-// in us a sweep, at a + 2b = 0.6 n: FP32 134 -> 191, FIX16 76 -> 95; 0.9 n: 191 -> 205,
-// 103 -> 107; 1.05 n: 219 -> 211, 117 -> 112; 1.5 n: 303 -> 230, 159 -> 131.  Lattice
-// neighbours and fewer replicas gain from 0.7 n on (FP32, 32 replicas 33 -> 21).
-bool round_pays(int32_t n, int64_t a, int64_t b) { return a + 2 * b > n; }
+// writes 2(a + b).  Few replicas are bound by their launches, of which a pass saves one.
+// Two such rounds on 60000 vertices, random partners, classes -> passes in us a sweep.
+// 1024 replicas, at a + 2b = 0.6 n: FP32 134 -> 191, FIX16 76 -> 95; 0.9 n: 191 -> 205,
+// 103 -> 107; 1.05 n: 219 -> 211, 117 -> 112; 1.5 n: 303 -> 230, 159 -> 131.  32 replicas,
+// 0.6 n: 26 -> 20, 27 -> 27; 0.9 n: 33 -> 23, 35 -> 32.
+constexpr int32_t kFewReplicas = 64;
+bool round_pays(int32_t n, int32_t R, int64_t a, int64_t b) {
+  return (R <= kFewReplicas ? 2 : 1) * (a + 2 * b) > n;
+}
 
 template <int ST, int VEC>
 int pass(cosm_state *s, int32_t q, const Entry *entries, int32_t rbeg, int32_t rend, float alpha,
@@ -243,7 +246,7 @@ int sweeps(cosm_state *s, int64_t n_sweeps) {
 
 bool dual_hbm_form(int32_t n, int64_t m, int32_t C, int32_t R, const cosm_params &p) {
   const int32_t pw = p.storage == COSM_STORE_FP32 || p.storage == COSM_STORE_FIX32 ? 1 : 2;
-  if (n < kVerticesMin || dual_hbm_entry_bytes(n, m, C) == 0 || p.update != COSM_UPDATE_SCS ||
+  if (n < kVerticesMin || dual_hbm_entry_bytes(n, m, C, R) == 0 || p.update != COSM_UPDATE_SCS ||
       (size_t)n * (size_t)R * (size_t)(4 / pw) > kAltBytesMax)
     return false;
   if (p.residency != COSM_RES_AUTO) return p.residency == COSM_RES_HBM;
@@ -252,11 +255,11 @@ bool dual_hbm_form(int32_t n, int64_t m, int32_t C, int32_t R, const cosm_params
                           (size_t)lds_capacity_bytes();
 }
 
-size_t dual_hbm_entry_bytes(int32_t n, int64_t m, int32_t C) {
-  // two classes that pay have at least (n + 1) / 2 edges (round_pays; b <= n / 2); with
-  // them the last round, for the twist.  A round has an entry for two vertices, and one
-  // for an odd one.
-  const int64_t pay = std::min<int64_t>(C / 2, 2 * m / ((int64_t)n + 1));
+size_t dual_hbm_entry_bytes(int32_t n, int64_t m, int32_t C, int32_t R) {
+  // two classes that pay have at least (n + 1) / 2 edges, or half of that for few
+  // replicas (round_pays; b <= n / 2); with them the last round, for the twist.  A round
+  // has an entry for two vertices, and one for an odd one.
+  const int64_t pay = std::min<int64_t>(C / 2, (R <= kFewReplicas ? 4 : 2) * m / ((int64_t)n + 1));
   if (pay == 0) return 0;
   return (size_t)std::min<int64_t>((C + 1) / 2, pay + 1) * ((size_t)n / 2 + 1) * sizeof(Entry);
 }
@@ -265,7 +268,7 @@ size_t dual_hbm_choose(cosm_state *s) {
   std::vector<uint8_t> pays((size_t)(s->C + 1) / 2, 0);
   size_t rounds = 0;
   for (int32_t q = 0; 2 * q + 1 < s->C; q++) {
-    pays[(size_t)q] = round_pays(s->n, s->class_sizes[(size_t)2 * q], s->class_sizes[(size_t)2 * q + 1]);
+    pays[(size_t)q] = round_pays(s->n, s->R, s->class_sizes[(size_t)2 * q], s->class_sizes[(size_t)2 * q + 1]);
     rounds += pays[(size_t)q];
   }
   if (rounds == 0) return 0;

@@ -20,5 +20,5 @@ def workspace(n, m, C, R=1, **kw):
 def test_many_small_classes(n, m, C):
     extra = workspace(n, m, C) - workspace(n, m, C, residency=3)  # 3: the plain form
     # a second phase buffer, and 16 bytes per vertex for each pair of classes that can hold
-    # half as many edges as there are vertices, and one more
-    assert extra <= 4 * n + (2 * m // n + 1) * 16 * (n + 2) + 4096
+    # a quarter as many edges as there are vertices, and one more
+    assert extra <= 4 * n + (4 * m // n + 1) * 16 * (n + 2) + 4096
