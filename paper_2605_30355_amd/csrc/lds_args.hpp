@@ -78,55 +78,6 @@ __device__ __forceinline__ void lds_rows_out(uint32_t *lds, const LdsArgs &a, in
   }
 }
 
-// Bias fields: one more conflict-free sub-sweep against the virtual spin at
-// phase 0, four rows per thread in flight.
-template <int ST, int W, bool LAZY>
-__device__ __forceinline__ void field_pass(uint32_t *lds, const LdsArgs &a, float alpha, int nth) {
-  using F = Fmt<ST>;
-  constexpr int RW = W * F::kPerWord;
-  for (int s0 = threadIdx.x; s0 < a.n_rows; s0 += 4 * nth) {
-    int32_t hv[4];
-    uint32_t w[4][W];
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-      hv[q] = s0 + q * nth < a.n_rows ? a.h_slot[s0 + q * nth] : 0;
-      if (hv[q] != 0) lds_load<W>(lds, s0 + q * nth, w[q]);
-    }
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-      if (hv[q] != 0) {
-        float v[RW];
-        F::template unpack<W>(w[q], v);
-        const float ah = alpha * (float)hv[q];
-#pragma unroll
-        for (int k = 0; k < RW; k++) field_update<ST, LAZY>(v[k], ah);
-        F::template pack<W>(v, w[q]);
-        lds_store<W>(lds, s0 + q * nth, w[q]);
-      }
-    }
-  }
-}
-
-// The twist as a pass of its own: four rows per thread in flight, all loads,
-// then the updates and stores.
-template <int ST, int W, bool LAZY>
-__device__ __forceinline__ void twist_pass(uint32_t *lds, int32_t n_rows, const TwistOps<ST, W> &op,
-                                           int nth) {
-  for (int s0 = threadIdx.x; s0 < n_rows; s0 += 4 * nth) {
-    uint32_t w[4][W];
-#pragma unroll
-    for (int q = 0; q < 4; q++)
-      if (s0 + q * nth < n_rows) lds_load<W>(lds, s0 + q * nth, w[q]);
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-      if (s0 + q * nth < n_rows) {
-        twist_row<ST, W, LAZY>(op, w[q]);
-        lds_store<W>(lds, s0 + q * nth, w[q]);
-      }
-    }
-  }
-}
-
 // Compile-time loop indices and flags for the unrolled class loops.
 template <int V>
 struct IntC {
