@@ -80,11 +80,11 @@ enum { COSM_STORE_FP32 = 0, COSM_STORE_FP16 = 1, COSM_STORE_BF16 = 2, COSM_STORE
        COSM_STORE_FIX32 = 4, COSM_STORE_FP16_PK = 5 };
 /* Where a replica's phases live during a sweep.  LDS: a workgroup holds whole
  * replicas in LDS for all sweeps of a call.  HBM: phases stay in device memory,
- * one launch per colour class (two per launch on graphs past the LDS, which then
- * need a second phase buffer).  PLAIN: one replica per launch, one launch per
- * colour class (the unbatched baseline).  AUTO: LDS where a replica fits (with
- * FULL_GRADIENT where two copies of it do, and the replicas keep enough CUs busy),
- * else HBM. */
+ * one launch per colour class (two per launch on graphs past the LDS, where the
+ * classes are large and there is room for a second phase buffer).  PLAIN: one
+ * replica per launch, one launch per colour class (the unbatched baseline).  AUTO:
+ * LDS where a replica fits (with FULL_GRADIENT where two copies of it do, and the
+ * replicas keep enough CUs busy), else HBM. */
 enum { COSM_RES_AUTO = 0, COSM_RES_LDS = 1, COSM_RES_HBM = 2, COSM_RES_PLAIN = 3 };
 /* GRID: every phase, step and angle is a multiple of 2^-23 turn (2^-16 with
  * FIX16 storage), so sweeps are exact; the window must be a multiple of 2^-22
@@ -389,8 +389,10 @@ typedef struct {
                               the same bit for bit), FP16 / BF16 / FP16_PK in every form (the
                               centred value y then lies in (-1, 1) between twists).
                               FP32 in the LDS forms on the grid schedule leaves the wrap to
-                              the twists up to a bound of one turn, with the same result;
-                              this field keeps to the 1/2-turn bound */
+                              the twists up to wider bounds (one turn of drift; where an
+                              edge is decided at either of its ends, differences of less
+                              than two turns), with the same result; this field keeps to
+                              the 1/2-turn bound */
 } cosm_info;
 int cosm_get_info(const cosm_state *s, cosm_info *out);
 
