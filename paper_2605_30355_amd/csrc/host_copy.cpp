@@ -123,8 +123,8 @@ int copy_long(hipStream_t stream, Block *b, char *dst, const char *src, size_t b
     if (at < l)
       std::memcpy(dst + c * kChunk + at, b->mem + (c % kChunks) * kChunk + at, std::min(p, l - at));
   };
-  // While the device has work left (sweeps may take seconds) the threads sleep until the
-  // first chunk is there; then they follow the chunks, some tens of us apart.
+  // While the device has work left (sweeps may take seconds) the threads sleep; they wake
+  // while the first chunk is on its way and follow the chunks, some tens of us apart.
   std::mutex mu;
   std::condition_variable first;
   bool go = idle;
@@ -164,6 +164,9 @@ int copy_long(hipStream_t stream, Block *b, char *dst, const char *src, size_t b
     of = 1;
   }
   hipError_t err = hipSuccess;
+  // (the last event is not a chunk's before the first has arrived)
+  const hipEvent_t before = b->ev[kChunks - 1];
+  if (!idle) err = hipEventRecord(before, stream);
   size_t issued = 0, arrived = 0;
   while (arrived < n && err == hipSuccess) {
     // a chunk's place is free once every thread has emptied the one before it
@@ -176,12 +179,15 @@ int copy_long(hipStream_t stream, Block *b, char *dst, const char *src, size_t b
       if (err == hipSuccess) err = hipEventRecord(b->ev[issued % kChunks], stream);
       issued++;
     }
+    if (err == hipSuccess && arrived == 0 && !idle) {
+      err = hipEventSynchronize(before);
+      start();
+    }
     if (err == hipSuccess) err = hipEventSynchronize(b->ev[arrived % kChunks]);
     if (err != hipSuccess) break;
     if (workers.empty()) part(arrived, 0, 1);
     arrived++;
     ready.store(arrived, std::memory_order_release);
-    if (arrived == 1) start();
   }
   if (err != hipSuccess) {
     stop.store(true);
@@ -208,8 +214,11 @@ int plain(hipStream_t stream, const HostPiece *p, int count) {
 int copy_to_host(hipStream_t stream, HostPiece *p, int count, bool may_allocate) {
   Block *b = may_allocate ? take_block(stream) : nullptr;
   if (b == nullptr) return plain(stream, p, count);
-  const bool idle = hipStreamQuery(stream) == hipSuccess;
-  if (!idle) (void)hipGetLastError();  // (not ready is no error)
+  bool idle = true;  // (asked only where it matters: the question takes some 8 us)
+  if (std::any_of(p, p + count, [](const HostPiece &x) { return x.bytes >= kLong; })) {
+    idle = hipStreamQuery(stream) == hipSuccess;
+    if (!idle) (void)hipGetLastError();  // (not ready is no error)
+  }
   std::sort(p, p + count, [](const HostPiece &x, const HostPiece &y) { return x.src < y.src; });
   // the short pieces: neighbours in one copy, waited for with the long ones' or last
   char *const shorts = b->mem + kChunkMax * kChunks;
